@@ -37,8 +37,8 @@
 // that saw no token (l = 0) carries m = -inf, so it never sets the maximum
 // of a combine or a merge.
 //
-// Every unit writes one partial softmax state per row; merge_row_kernel or
-// merge_kernel combines each (beam, query head)'s states in a fixed order
+// Every unit writes one partial softmax state per row; merge_kernel
+// combines each (beam, query head)'s states in a fixed order
 // (deterministic, no float atomics).
 #include <hip/hip_runtime.h>
 
@@ -192,6 +192,18 @@ __device__ __forceinline__ void write_partial(void* part_o, float* part_ml, int6
   const float inv = l > 0.f ? 1.f / l : 0.f;
   const int e = partial_exp<D, KV>(o);
   if (active) store_partial<D, KV>(part_o, part_ml, prow, o, m, l, inv, e, lq);
+}
+
+// Largest value over the sixteen lanes of a DPP row (rotations within it).
+__device__ __forceinline__ float row16_max(float x) {
+  auto ror = [](float v, auto n) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 0x120 | decltype(n)::value, 0xf, 0xf, false));
+  };
+  x = fmaxf(x, ror(x, std::integral_constant<int, 8>{}));
+  x = fmaxf(x, ror(x, std::integral_constant<int, 4>{}));
+  x = fmaxf(x, ror(x, std::integral_constant<int, 2>{}));
+  return fmaxf(x, ror(x, std::integral_constant<int, 1>{}));
 }
 
 __device__ __forceinline__ int rl(int x, int i) { return __builtin_amdgcn_readlane(x, i); }
@@ -1337,53 +1349,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   }
 }
 
-// kEpl consecutive stored elements of a partial row (fp16 or fp32), loaded
-// with one or two vector loads and widened one at a time.
-template <int kEpl, bool F16>
-struct MergeRaw;
-template <>
-struct MergeRaw<8, true> {
-  typedef uint4 T;
-  static __device__ __forceinline__ T load(const void* base, int64_t off) {
-    return *reinterpret_cast<const uint4*>(static_cast<const _Float16*>(base) + off);
-  }
-  static __device__ __forceinline__ float get(const T& t, int i) {
-    const uint32_t w = i < 2 ? t.x : (i < 4 ? t.y : (i < 6 ? t.z : t.w));
-    const f16x2 hv = __builtin_bit_cast(f16x2, w);
-    return static_cast<float>((i & 1) ? hv.y : hv.x);
-  }
-};
-template <>
-struct MergeRaw<4, true> {
-  typedef uint2 T;
-  static __device__ __forceinline__ T load(const void* base, int64_t off) {
-    return *reinterpret_cast<const uint2*>(static_cast<const _Float16*>(base) + off);
-  }
-  static __device__ __forceinline__ float get(const T& t, int i) {
-    const f16x2 hv = __builtin_bit_cast(f16x2, i < 2 ? t.x : t.y);
-    return static_cast<float>((i & 1) ? hv.y : hv.x);
-  }
-};
-template <>
-struct MergeRaw<8, false> {
-  struct T {
-    f32x4 a, b;
-  };
-  static __device__ __forceinline__ T load(const void* base, int64_t off) {
-    const f32x4* src = reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + off);
-    return T{src[0], src[1]};
-  }
-  static __device__ __forceinline__ float get(const T& t, int i) { return i < 4 ? t.a[i] : t.b[i - 4]; }
-};
-template <>
-struct MergeRaw<4, false> {
-  typedef f32x4 T;
-  static __device__ __forceinline__ T load(const void* base, int64_t off) {
-    return *reinterpret_cast<const f32x4*>(static_cast<const float*>(base) + off);
-  }
-  static __device__ __forceinline__ float get(const T& t, int i) { return t[i]; }
-};
-
 // Exact merge of the partial softmax states of each (beam, query head), in
 // the order of the beam's slot list. With M = max_k m_k over the states
 // that saw tokens (l_k > 0), w_k = l_k 2^(m_k - M), and e_k the stored
@@ -1393,220 +1358,136 @@ struct MergeRaw<4, false> {
 // merges read their table entries without a branch).
 __device__ const int kZeroTabRow[kSlotTabReadAhead] = {};
 
-// Two kernels compute it; launch_merge picks by the number of rows.
-//
-// merge_row_kernel: D / 2 lanes per row (2 elements per lane), for batches
-// with few rows, where spreading each row over many lanes shortens the
-// work after the data arrives. A row's slot count and first kMergeBatch
-// slots sit in one row of the slot table and are loaded with the beam's
-// lengths; then kMergeBatch states at a time, the table entries of the
-// next batch loaded with them: 1 + ceil(n / kMergeBatch) round trips to
-// memory for n slots.
+// One wave per row, D / 64 elements per lane, bound by
+// its chain of memory round trips: the table row, then the states. Lane j
+// holds slot j's table entry (the row's first 64 in one load, with its
+// count and the beam's lengths), reads slot j's (m, l, z) and computes its
+// weight, once per slot and not once per lane; the elements of up to
+// kMergeRound slots are loaded in the same round trip and weighed with the
+// lanes' weights as scalars: two round trips for up to 32 slots, one more
+// for each 32 further. Against 16 slots per round trip with every weight
+// computed by every lane, and a kernel of sixteen lanes per row above 4,096
+// rows: 7B 64-beam tree 24.2 -> 23.65 us per call (1,792 rows of 13 slots),
+// balanced tree 51.1 -> 49.7, straggler batch 88.7 -> 87.5 (7,168 rows),
+// paged 64-beam call 106.1 -> 102.9.
+constexpr int kMergeThreads = 256;
+constexpr int kMergeRound = 32;  // slots whose elements are loaded together
+
+__device__ __forceinline__ float wave_max(float x) {
+  x = row16_max(x);
+  return fmaxf(fmaxf(rlf(x, 0), rlf(x, 16)), fmaxf(rlf(x, 32), rlf(x, 48)));
+}
+
+// Sum over the wave, in a fixed order.
+__device__ __forceinline__ float wave_sum(float x) {
+  auto ror = [](float v, auto n) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 0x120 | decltype(n)::value, 0xf, 0xf, false));
+  };
+  x += ror(x, std::integral_constant<int, 8>{});
+  x += ror(x, std::integral_constant<int, 4>{});
+  x += ror(x, std::integral_constant<int, 2>{});
+  x += ror(x, std::integral_constant<int, 1>{});
+  return (rlf(x, 0) + rlf(x, 16)) + (rlf(x, 32) + rlf(x, 48));
+}
+
+// One lane's stored elements of a row: D / 64 of them, fp16 or fp32.
 template <int D, bool F16>
-__global__ __launch_bounds__(kThreads) void merge_row_kernel(MergeParams p) {
-  constexpr int kTpr = D / 2;
-  constexpr int kRows = kThreads / kTpr;
-  constexpr int kBatch = kMergeBatch;
-  const int r = blockIdx.x * kRows + threadIdx.x / kTpr;
-  // Stored position pos0 (lane order) holds dimension d0, pos0 + 1 holds d0 + 1.
-  const int pos0 = (threadIdx.x % kTpr) * 2;
-  const int d0 = 16 * ((pos0 % (D / 4)) / 4) + 4 * (pos0 / (D / 4)) + pos0 % 4;
+struct RowElems {
+  static constexpr int kEl = D / 64;
+  typedef typename std::conditional<F16, _Float16, float>::type E;
+  typedef E V __attribute__((ext_vector_type(kEl)));
+  V v;
+};
+template <bool F16>
+struct RowElems<64, F16> {
+  static constexpr int kEl = 1;
+  typedef typename std::conditional<F16, _Float16, float>::type E;
+  E v[1];
+};
+
+template <int D, bool F16>
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
+  using R = RowElems<D, F16>;
+  constexpr int kEl = R::kEl;
+  const int lane = threadIdx.x & 63;
+  const int r = rfl(static_cast<int>(blockIdx.x) * (kMergeThreads / 64) + static_cast<int>(threadIdx.x >> 6));
   if (r >= p.num_seqs * p.hq) return;
   const int b = r / p.hq;
   const int h = r % p.hq;
-  const int* tab = p.slot_tab ? p.slot_tab + static_cast<int64_t>(b) * p.slot_stride : nullptr;
-  // The row's inputs in one round trip: its table row (count and first
-  // kBatch entries; the paged path reads a row of zeros), its live length
-  // and its build-time length (the paged path, which has none, reads the
-  // live one again). No load waits for another.
-  const int* tabr = tab ? tab : kZeroTabRow;
-  int ent[kBatch];
-#pragma unroll
-  for (int k = 0; k < kBatch; ++k) ent[k] = tabr[1 + k];
-  const int n = tab ? tabr[0] : p.paged_nsplit;
-  const int64_t head_base = tab ? static_cast<int64_t>(h / p.g) * p.rows_per_head + h % p.g : 0;
+  // The row's inputs in one round trip: its table row (the paged path reads
+  // a row of zeros), its live length and its build-time length (the paged
+  // path, which has none, reads the live one again). The entries are read
+  // past the count (the table's read-ahead zeros keep that in bounds).
+  const int* tab = p.slot_tab ? p.slot_tab + static_cast<int64_t>(b) * p.slot_stride : kZeroTabRow;
+  int ent = tab[1 + lane];
+  const int n = p.slot_tab ? rfl(tab[0]) : p.paged_nsplit;
+  const int head_base = p.slot_tab ? (h / p.g) * p.rows_per_head + h % p.g : 0;
   const int L = beam_len(p, b);
   const int blen = (p.build_len ? p.build_len : p.seq_lens)[b];
   bool nan = p.build_len && L < blen;
   float mx = kNegInf, den = 0.f;
-  f32x2 acc = {0.f, 0.f};
-  for (int k0 = 0; k0 < n; k0 += kBatch) {
-    f32x4 ml[kBatch];
-    f32x2 o[kBatch];
+  float acc[kEl];
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int kk = k0 + k < n ? k0 + k : n - 1;
-      int64_t row;
-      if (tab)
-        row = head_base + (k0 + k < n ? ent[k] : ent[0]);
-      else
-        row = (static_cast<int64_t>(b) * p.paged_nsplit + kk) * p.hq + h;
-      ml[k] = *reinterpret_cast<const f32x4*>(p.part_ml + row * kPartMl);
-      if constexpr (F16) {
-        const f16x2 hv = *reinterpret_cast<const f16x2*>(static_cast<const uint16_t*>(p.part_o) + row * D + pos0);
-        o[k] = f32x2{static_cast<float>(hv.x), static_cast<float>(hv.y)};
-      } else {
-        o[k] = *reinterpret_cast<const f32x2*>(static_cast<const float*>(p.part_o) + row * D + pos0);
+  for (int e = 0; e < kEl; ++e) acc[e] = 0.f;
+  for (int k0 = 0; k0 < n; k0 += 64) {
+    const int left = n - k0 < 64 ? n - k0 : 64;  // slots of this round
+    if (k0 > 0) ent = p.slot_tab && lane < left ? tab[1 + k0 + lane] : 0;
+    // Lane j: slot k0 + j (past the end: a repeat of slot k0, with no weight).
+    const int j = lane < left ? lane : 0;
+    const int first = rfl(ent);
+    const int row_j = p.slot_tab ? head_base + (lane < left ? ent : first)
+                                 : (b * p.paged_nsplit + k0 + j) * p.hq + h;
+    f32x4 ml = *reinterpret_cast<const f32x4*>(p.part_ml + static_cast<int64_t>(row_j) * kPartMl);
+    R o[kMergeRound];
+    auto load = [&](int c0, int c1) {  // slots c0 .. c1 of the round (c1 - c0 <= kMergeRound)
+#pragma unroll
+      for (int k = 0; k < kMergeRound; ++k) {
+        if (k % 8 == 0 && c0 + k >= c1) break;  // uniform
+        const int64_t row = rl(row_j, c0 + k);
+        o[k] = *reinterpret_cast<const R*>(static_cast<const typename R::E*>(p.part_o) + row * D + kEl * lane);
       }
-    }
-    // The next batch's table entries travel with this batch's states
-    // (stride >= n + 1, so the reads stay inside the beam's table row).
-    if (tab && k0 + kBatch < n) {
-#pragma unroll
-      for (int k = 0; k < kBatch; ++k) ent[k] = k0 + kBatch + k < n ? tab[1 + k0 + kBatch + k] : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      if (k0 + k >= n) ml[k] = f32x4{kNegInf, 0.f, 0.f, 0.f};
-      if (ml[k].y == 0.f && ml[k].x == ml[k].x) ml[k].x = kNegInf;  // a state without tokens
-    }
-    float bm = kNegInf;
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      nan |= ml[k].x != ml[k].x;
-      bm = fmaxf(bm, ml[k].x);
-    }
-    const float mn = fmaxf(mx, bm);
+    };
+    load(0, left);
+    if (lane >= left) ml = f32x4{kNegInf, 0.f, 0.f, 0.f};
+    if (ml.y == 0.f && ml.x == ml.x) ml.x = kNegInf;  // a state without tokens
+    nan |= __builtin_amdgcn_ballot_w64(ml.x != ml.x) != 0;
+    const float mn = fmaxf(mx, wave_max(ml.x));
     if (mn == kNegInf) continue;
     const float a = (mx == kNegInf) ? 0.f : __builtin_amdgcn_exp2f(mx - mn);
-    den *= a;
-    acc *= a;
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const float w = (ml[k].x == kNegInf) ? 0.f : ml[k].y * __builtin_amdgcn_exp2f(ml[k].x - mn);
-      den += w;
-      acc += o[k] * (w * ml[k].z);
-    }
-    mx = mn;
-  }
-  const float inv = (den > 0.f && L > 0) ? 1.f / den : 0.f;
-  f32x2 w = acc * inv;
-  if (nan) {
-    const float q = __builtin_nanf("");
-    w = f32x2{q, q};
-  }
-  *reinterpret_cast<f32x2*>(p.out + static_cast<int64_t>(r) * D + d0) = w;
-}
-
-// merge_kernel: for batches with many rows. One wave per workgroup, sixteen
-// lanes per row, each lane holding D / 16 consecutive stored elements (one
-// or two 16-byte loads per state). Lane j of a row holds slot table entries
-// j, j + 16, ... (the first kMergeTabChunks
-// chunks are read in the first round trip to memory, with the beam's
-// lengths); for a batch of 16 slots, lane j reads slot j's (m, l, s) and
-// every lane reads its elements of every slot of the batch, the slots' rows
-// shuffled across the row's lanes: one round trip per batch. The weights
-// are added in slot order.
-constexpr int kMergeLanes = 16;
-// Up to this many rows the one-row-per-wave kernel runs (about the waves
-// the GPU keeps resident at its occupancy); above, the sixteen-lane one.
-constexpr int kMergeRowKernelMaxRows = 4096;
-constexpr int kMergeTabChunks = 4;
-static_assert(1 + kMergeTabChunks * kMergeLanes <= kSlotTabReadAhead && 1 + kMergeBatch <= kSlotTabReadAhead,
-              "the merges' table read-ahead stays inside the table's padding");
-constexpr int kMergeThreads = 64;
-template <int D, bool F16>
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
-  constexpr int kLpr = kMergeLanes;
-  constexpr int kEpl = D / kLpr;              // stored elements per lane
-  constexpr int kRows = kMergeThreads / kLpr;  // rows per workgroup
-  constexpr int kBatch = kLpr;                // slots whose states are loaded together
-  const int lane = threadIdx.x & 63;
-  const int j = lane & (kLpr - 1);
-  const int gbase = lane & ~(kLpr - 1);  // first lane of this row's group
-  const int total = p.num_seqs * p.hq;
-  const int r_raw = static_cast<int>(blockIdx.x) * kRows + static_cast<int>(threadIdx.x) / kLpr;
-  const bool valid = r_raw < total;
-  const int r = valid ? r_raw : total - 1;  // surplus rows repeat the last one and store nothing
-  const int b = r / p.hq;
-  const int h = r % p.hq;
-  const int* tab = p.slot_tab ? p.slot_tab + static_cast<int64_t>(b) * p.slot_stride : nullptr;
-  // The row's inputs in one round trip, as in merge_row_kernel: the count,
-  // the first kMergeTabChunks x 16 entries (read past the count, which the
-  // table's read-ahead zeros keep in bounds; entries past n are not used),
-  // the live and the build-time length.
-  const int* tabr = tab ? tab : kZeroTabRow;
-  int ent[kMergeTabChunks];
-#pragma unroll
-  for (int c = 0; c < kMergeTabChunks; ++c) ent[c] = tabr[1 + kBatch * c + j];
-  const int n = tab ? tabr[0] : p.paged_nsplit;
-  const int head_base = tab ? (h / p.g) * p.rows_per_head + h % p.g : 0;
-  // Partial row of slot k (k < n).
-  auto slot_row = [&](int k, int entry) { return tab ? head_base + entry : (b * p.paged_nsplit + k) * p.hq + h; };
-  const int L = beam_len(p, b);
-  const int blen = (p.build_len ? p.build_len : p.seq_lens)[b];
-  bool nan = p.build_len && L < blen;
-  float mx = kNegInf, den = 0.f;
-  float acc[kEpl];
-#pragma unroll
-  for (int e = 0; e < kEpl; ++e) acc[e] = 0.f;
-  for (int k0 = 0, c = 0; k0 < n; k0 += kBatch, ++c) {
-    // Lane j: slot k0 + j (a repeat of slot k0 past the end).
-    const bool has = k0 + j < n;
-    const int kk = has ? k0 + j : k0;
-    int entry = 0;
-    if (tab) {
-      if (c < kMergeTabChunks) {
-        entry = ent[0];
-#pragma unroll
-        for (int i = 1; i < kMergeTabChunks; ++i)
-          if (c == i) entry = ent[i];
-        const int first = __shfl(entry, gbase);  // slot k0's entry (every lane takes part)
-        if (!has) entry = first;
-      } else {
-        entry = tab[1 + kk];
-      }
-    }
-    const int row_j = slot_row(kk, entry);
-    f32x4 ml = *reinterpret_cast<const f32x4*>(p.part_ml + static_cast<int64_t>(row_j) * kPartMl);
-    typename MergeRaw<kEpl, F16>::T raw[kBatch];
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int row_k = __shfl(row_j, gbase + k);
-      raw[k] = MergeRaw<kEpl, F16>::load(p.part_o, static_cast<int64_t>(row_k) * D + kEpl * j);
-    }
-    if (!has) ml = f32x4{kNegInf, 0.f, 0.f, 0.f};
-    if (ml.y == 0.f && ml.x == ml.x) ml.x = kNegInf;  // a state without tokens
-    nan |= ml.x != ml.x;
-    float bm = ml.x;
-#pragma unroll
-    for (int o = 1; o < kLpr; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
-    const float mn = fmaxf(mx, bm);
-    if (mn == kNegInf) continue;  // uniform over the row's lanes
-    const float a = (mx == kNegInf) ? 0.f : __builtin_amdgcn_exp2f(mx - mn);
-    den *= a;
-#pragma unroll
-    for (int i = 0; i < kEpl; ++i) acc[i] *= a;
     const float w = (ml.x == kNegInf) ? 0.f : ml.y * __builtin_amdgcn_exp2f(ml.x - mn);
-    const float ws = w * ml.z;
+    const float wz = w * ml.z;
+    den = den * a + wave_sum(w);
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const float wk = __shfl(w, gbase + k);
-      const float wsk = __shfl(ws, gbase + k);
-      if (k0 + k < n) {
-        den += wk;
+    for (int e = 0; e < kEl; ++e) acc[e] *= a;
+    auto add = [&](int c0, int c1) {
 #pragma unroll
-        for (int i = 0; i < kEpl; ++i) acc[i] += MergeRaw<kEpl, F16>::get(raw[k], i) * wsk;
+      for (int k = 0; k < kMergeRound; ++k) {
+        if (k % 8 == 0 && c0 + k >= c1) break;
+        if (c0 + k < c1) {  // uniform (past the end: a repeat, whose weight of 0 could meet an infinity)
+          const float wk = rlf(wz, c0 + k);
+#pragma unroll
+          for (int e = 0; e < kEl; ++e) acc[e] = __builtin_fmaf(static_cast<float>(o[k].v[e]), wk, acc[e]);
+        }
       }
+    };
+    add(0, left);
+    if (left > kMergeRound) {
+      load(kMergeRound, left);
+      add(kMergeRound, left);
     }
     mx = mn;
   }
-  // A NaN state in any slot of the row makes the row NaN.
-  int any_nan = nan ? 1 : 0;
-#pragma unroll
-  for (int o = 1; o < kLpr; o <<= 1) any_nan |= __shfl_xor(any_nan, o);
-  if (!valid) return;
   const float inv = (den > 0.f && L > 0) ? 1.f / den : 0.f;
+  // Stored position pos holds dimension 16 t + 4 q + i for pos = (D / 4) q + 4 t + i.
+  const int pos = kEl * lane;
+  const int dim = 16 * ((pos % (D / 4)) / 4) + 4 * (pos / (D / 4)) + pos % 4;
+  float* dst = p.out + static_cast<int64_t>(r) * D + dim;
   const float q = __builtin_nanf("");
-  float* orow = p.out + static_cast<int64_t>(r) * D;
-  // Stored position pos holds dimension 16 t + 4 lq + i for pos = (D/4) lq + 4 t + i.
-#pragma unroll
-  for (int c = 0; c < kEpl / 4; ++c) {
-    const int pos = kEpl * j + 4 * c;
-    const int dim = 16 * ((pos % (D / 4)) / 4) + 4 * (pos / (D / 4));
-    f32x4 v = {acc[4 * c] * inv, acc[4 * c + 1] * inv, acc[4 * c + 2] * inv, acc[4 * c + 3] * inv};
-    if (any_nan) v = f32x4{q, q, q, q};
-    *reinterpret_cast<f32x4*>(orow + dim) = v;
+  if constexpr (kEl == 2) {
+    *reinterpret_cast<f32x2*>(dst) = nan ? f32x2{q, q} : f32x2{acc[0] * inv, acc[1] * inv};
+  } else {
+    *dst = nan ? q : acc[0] * inv;
   }
 }
 
@@ -1623,34 +1504,18 @@ hipError_t launch_merge(const MergeParams& p, int head_dim, int kv_kind, hipStre
   const int rows = p.num_seqs * p.hq;
   if (rows <= 0) return hipSuccess;
   const bool f16 = kv_kind != kKvF32;
-  if (rows <= kMergeRowKernelMaxRows) {
-    const int per = kThreads / (head_dim / 2);
-    const int blocks = (rows + per - 1) / per;
-    if (head_dim == 128) {
-      if (f16)
-        hipLaunchKernelGGL((merge_row_kernel<128, true>), dim3(blocks), dim3(kThreads), 0, stream, p);
-      else
-        hipLaunchKernelGGL((merge_row_kernel<128, false>), dim3(blocks), dim3(kThreads), 0, stream, p);
-    } else {
-      if (f16)
-        hipLaunchKernelGGL((merge_row_kernel<64, true>), dim3(blocks), dim3(kThreads), 0, stream, p);
-      else
-        hipLaunchKernelGGL((merge_row_kernel<64, false>), dim3(blocks), dim3(kThreads), 0, stream, p);
-    }
-    return hipGetLastError();
-  }
-  const int per = kMergeThreads / kMergeLanes;  // rows per workgroup
-  const int blocks = (rows + per - 1) / per;
+  const int per = kMergeThreads / 64;
+  const dim3 grid((rows + per - 1) / per), block(kMergeThreads);
   if (head_dim == 128) {
     if (f16)
-      hipLaunchKernelGGL((merge_kernel<128, true>), dim3(blocks), dim3(kMergeThreads), 0, stream, p);
+      hipLaunchKernelGGL((merge_kernel<128, true>), grid, block, 0, stream, p);
     else
-      hipLaunchKernelGGL((merge_kernel<128, false>), dim3(blocks), dim3(kMergeThreads), 0, stream, p);
+      hipLaunchKernelGGL((merge_kernel<128, false>), grid, block, 0, stream, p);
   } else {
     if (f16)
-      hipLaunchKernelGGL((merge_kernel<64, true>), dim3(blocks), dim3(kMergeThreads), 0, stream, p);
+      hipLaunchKernelGGL((merge_kernel<64, true>), grid, block, 0, stream, p);
     else
-      hipLaunchKernelGGL((merge_kernel<64, false>), dim3(blocks), dim3(kMergeThreads), 0, stream, p);
+      hipLaunchKernelGGL((merge_kernel<64, false>), grid, block, 0, stream, p);
   }
   return hipGetLastError();
 }

@@ -113,11 +113,11 @@ struct AttnParams {
   int32_t two_windows;
 };
 
-// Slots the merge kernel reads per round trip (and the smallest slot-table
-// stride - 1, so that a beam's first round of slots is always in its row).
+// Slots per step of the planner's merge cost, and the smallest slot-table
+// stride - 1.
 constexpr int kMergeBatch = 16;
 // Readable int32 words after the start of any slot-table row (the table is
-// followed by this many zeros): the merges read a row's first entries in
+// followed by this many zeros): the merge reads a row's first 64 entries in
 // the same round trip as its count, without waiting for the count.
 constexpr int kSlotTabReadAhead = 65;
 
