@@ -373,7 +373,7 @@ tts_status tts_plan_units_host(int32_t num_reqs, const int32_t* req_seq_offsets,
     if (r.nrows <= 0) continue;
     const int32_t u = static_cast<int32_t>(units++);
     const int32_t nbeams = r.nrows / g;
-    if (r.mode == tts::kModeWide) {
+    if ((r.mode & 0xff) == tts::kModeWide) {
       for (int32_t e = 0; e < r.nstatic; ++e) {
         const int32_t second = e >= tts::kMaxEntries;
         const int32_t id = second ? r.ent_id2[e - tts::kMaxEntries] : r.ent_id[e];

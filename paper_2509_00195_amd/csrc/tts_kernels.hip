@@ -1,16 +1,31 @@
 // HIP kernels (gfx950) for prefix-shared beam decode attention.
 //
-// attn_kernel: one workgroup (4 waves) per compute unit walks a chain of
-// work units (tts_work.h), each the query rows of whole beams for one KV
-// head against a list of KV blocks (up to 128, in two windows of 64).
-//  * Narrow units (up to 64 rows, 4 row tiles of 16): every wave keeps the
-//    softmax state of all of the unit's rows in registers and streams its
-//    own share of the block pairs (pairs w, w + 4, ...) straight from HBM
-//    into registers, one pair ahead of the one it computes; no LDS staging
-//    and no barriers until the four waves combine their states.
-//  * Wide units (a segment shared by many beams, up to 192 rows): each block
-//    pair is loaded once, a quarter per wave, staged in LDS and read by all
-//    four waves, each running its own row tiles.
+// attn_kernel: one workgroup (8 waves, two per SIMD) per compute unit walks a
+// chain of work units (tts_work.h), each the query rows of whole beams for
+// one KV head against a list of KV blocks (up to 128, in two windows of 64).
+//  * Narrow units (up to 64 rows): every wave keeps the softmax state of two
+//    row tiles (16 rows each) in registers and streams its own share of the
+//    block pairs straight from HBM into registers; no LDS staging and no
+//    barriers until the waves combine their states. Up to 32 rows all eight
+//    waves split the pairs; more rows make two groups of waves, each with
+//    the pairs of its rows.
+//  * Wide units (a segment shared by many beams, up to 256 rows): each block
+//    pair is loaded once, an eighth per wave, staged in LDS two pairs at a
+//    time and read from there. Up to 128 rows, each half of the waves takes
+//    one pair of every step for all rows; above, every wave takes every pair
+//    for its own two row tiles.
+// Two waves per SIMD, because a wave's step is a chain (scores, softmax,
+// value product) that leaves the matrix cores and the vector units idle in
+// turn: with four waves of up to three tiles a wide unit of 11 row tiles took
+// 0.61 us per block, against 0.30 (7B 64-beam tree); fp8 units of 7 tiles
+// 0.47 against 0.40 (long chain). At 256 registers per wave nothing may spill:
+// scratch stores alone took 8 to 25 us per launch. Against four waves: long
+// chain (fp8) 342 -> 285 us per call, paged 64-beam call 103 -> 92.5, 7B
+// 64-beam tree 23.65 -> 22.5, straggler batch 87.5 -> 85.1, verification of
+// four tokens 46.9 -> 42.5. Bound by the memory where tails stream (balanced
+// tree, 5.3 TB/s of unique KV, unchanged), by LDS reads and vector issue in
+// wide units, and by the units' round trips and the second launch in small
+// batches.
 //
 // Products on MFMA, two 16-token blocks ("a pair") at a time, per row tile:
 //   S^T = K Q^T   : 2 x 4 v_mfma_f32_16x16x32_bf16 (M = 16 tokens, N = 16
@@ -32,7 +47,7 @@
 // fp32 accumulators or underflow every weight), its pairs are computed again
 // with m_ref = that row's exact maximum: per wave in narrow units (no
 // barrier inside their loop), by the whole workgroup in wide units (whose
-// loop holds barriers, so the decision is taken over all four waves).
+// loop holds barriers, so the decision is taken over all eight waves).
 // Either way each row ends with a consistent (m_ref, l, o) triple; a state
 // that saw no token (l = 0) carries m = -inf, so it never sets the maximum
 // of a combine or a merge.
@@ -70,10 +85,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kTok = 16;  // tokens per KV block
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kUnitWaves;
+constexpr int kWaves = kThreads / 64;
 constexpr int kTiles = kMaxRows / 16;
-constexpr int kWideTiles = kMaxWideRows / 16 / 4;  // row tiles per wave in a wide unit
+constexpr int kWideTiles = kMaxWideRows / 16 / kWaves;  // row tiles per wave in a wide unit
+constexpr int kStepPairs = 2;                           // block pairs a wide unit stages between two barriers
 constexpr float kNegInf = -__builtin_inff();
 constexpr float kInf = __builtin_inff();
 constexpr float kRefWindow = 64.0f;  // |row max| (log2 units) handled with m_ref = 0
@@ -185,15 +201,6 @@ __device__ __forceinline__ void store_partial(void* part_o, float* part_ml, int6
   if (lq == 0) *reinterpret_cast<f32x4*>(part_ml + prow * kPartMl) = f32x4{m_out, l, z, 0.f};
 }
 
-// Both steps for one row; `active` says whether the row exists.
-template <int D, int KV>
-__device__ __forceinline__ void write_partial(void* part_o, float* part_ml, int64_t prow, const f32x4 (&o)[D / 16],
-                                              float m, float l, int lq, bool active) {
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  const int e = partial_exp<D, KV>(o);
-  if (active) store_partial<D, KV>(part_o, part_ml, prow, o, m, l, inv, e, lq);
-}
-
 // Largest value over the sixteen lanes of a DPP row (rotations within it).
 __device__ __forceinline__ float row16_max(float x) {
   auto ror = [](float v, auto n) {
@@ -204,6 +211,48 @@ __device__ __forceinline__ float row16_max(float x) {
   x = fmaxf(x, ror(x, std::integral_constant<int, 4>{}));
   x = fmaxf(x, ror(x, std::integral_constant<int, 2>{}));
   return fmaxf(x, ror(x, std::integral_constant<int, 1>{}));
+}
+
+// The same state from sixteen lanes of a wave's DPP row, lane c holding
+// stored elements (D / 16) c .. (all sixteen call together; `active` says
+// whether the row exists).
+template <int D, int KV>
+__device__ __forceinline__ void store_partial_row(void* part_o, float* part_ml, int64_t prow, const f32x4 (&o)[D / 64],
+                                                  float m, float l, float inv, int c, bool active) {
+  constexpr int kEl = D / 16;
+  float z = 1.f;
+  if constexpr (KV != kKvF32) {
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < kEl / 4; ++e)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) amax = fmaxf(amax, __builtin_fabsf(o[e][j]));
+    amax = row16_max(amax);
+    const int e2 = (amax > 0.f && amax <= 3.0e38f) ? __builtin_amdgcn_frexp_expf(amax) : 0;
+    uint32_t w[kEl / 2];
+#pragma unroll
+    for (int e = 0; e < kEl / 4; ++e)
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) {
+        const f16x2 h = {static_cast<_Float16>(__builtin_ldexpf(o[e][j], -e2)),
+                         static_cast<_Float16>(__builtin_ldexpf(o[e][j + 1], -e2))};
+        w[2 * e + j / 2] = __builtin_bit_cast(uint32_t, h);
+      }
+    if (active) {
+      uint16_t* dst = static_cast<uint16_t*>(part_o) + prow * D + kEl * c;
+      if constexpr (kEl == 8)
+        *reinterpret_cast<uint4*>(dst) = uint4{w[0], w[1], w[2], w[3]};
+      else
+        *reinterpret_cast<uint2*>(dst) = uint2{w[0], w[1]};
+    }
+    z = __builtin_ldexpf(inv, e2);
+  } else if (active) {
+    f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(part_o) + prow * D + kEl * c);
+#pragma unroll
+    for (int e = 0; e < kEl / 4; ++e) dst[e] = o[e] * inv;
+  }
+  const float m_out = (l > 0.f || m != m) ? m : kNegInf;
+  if (active && c == 0) *reinterpret_cast<f32x4*>(part_ml + prow * kPartMl) = f32x4{m_out, l, z, 0.f};
 }
 
 __device__ __forceinline__ int rl(int x, int i) { return __builtin_amdgcn_readlane(x, i); }
@@ -220,12 +269,21 @@ __device__ __forceinline__ int pair_token(int t, int m) { return ((m >> 2) << 3)
 //            or 16j + 4lq .. + 4 (fp32);
 //   v[dt]  : V of dim 16dt + ln, tokens 8lq .. 8lq + 7 of the pair.
 template <int D, int KV>
-struct Ops {
+struct KOps {
   static constexpr bool f32 = KV == kKvF32;
   static constexpr int kk = f32 ? D / 16 : D / 32;
   typedef typename std::conditional<f32, f32x4, uint4>::type T;
   T k[2][kk];
+};
+template <int D, int KV>
+struct VOps {
+  static constexpr bool f32 = KV == kKvF32;
+  typedef typename std::conditional<f32, f32x4, uint4>::type T;
   T v[D / 16][f32 ? 2 : 1];
+};
+template <int D, int KV>
+struct Ops : KOps<D, KV>, VOps<D, KV> {
+  typedef typename KOps<D, KV>::T T;
 };
 
 // fp8 caches load raw codes (half the registers) and convert per pair.
@@ -240,51 +298,66 @@ struct Fp8Frags {
 template <int D, int KV>
 using Frags = typename std::conditional<KV == kKvFp8, Fp8Frags<D>, Ops<D, KV>>::type;
 
-// standin: every load reads the first bytes of kb0 instead (a placeholder
-// whose data is never used).
 template <int D, int KV>
-__device__ __forceinline__ void load_pair(Frags<D, KV>& f, const unsigned char* kb0, const unsigned char* kb1,
-                                          const unsigned char* vb0, const unsigned char* vb1, int ln, int lq,
-                                          bool standin = false) {
+__device__ __forceinline__ void load_k(Frags<D, KV>& f, const unsigned char* kb0, const unsigned char* kb1, int ln,
+                                       int lq) {
   using G = Geo<D, KV>;
   using F = Frags<D, KV>;
   typedef typename F::T T;
-  auto at = [&](const unsigned char* a) { return reinterpret_cast<const T*>(standin ? kb0 : a); };
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int tok = pair_token(t, ln);
     const unsigned char* kr = (tok < 16 ? kb0 : kb1) + (tok & 15) * G::row_bytes;
 #pragma unroll
-    for (int j = 0; j < F::kk; ++j) {
-      if constexpr (KV == kKvFp8)
-        f.k[t][j] = *at(kr + 32 * j + 8 * lq);
-      else
-        f.k[t][j] = *at(kr + (4 * j + lq) * 16);
-    }
+    for (int j = 0; j < F::kk; ++j)
+      f.k[t][j] = *reinterpret_cast<const T*>(kr + (KV == kKvFp8 ? 32 * j + 8 * lq : (4 * j + lq) * 16));
   }
+}
+
+template <int D, int KV>
+__device__ __forceinline__ void load_v(Frags<D, KV>& f, const unsigned char* vb0, const unsigned char* vb1, int ln,
+                                       int lq) {
+  using G = Geo<D, KV>;
+  typedef typename Frags<D, KV>::T T;
   const unsigned char* vb = (lq >= 2 ? vb1 : vb0) + (lq & 1) * 8 * G::eb + ln * G::vrow_bytes;
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) {
     const unsigned char* vr = vb + 16 * dt * G::vrow_bytes;
-    f.v[dt][0] = *at(vr);
-    if constexpr (KV == kKvF32) f.v[dt][1] = *at(vr + 16);
+    f.v[dt][0] = *reinterpret_cast<const T*>(vr);
+    if constexpr (KV == kKvF32) f.v[dt][1] = *reinterpret_cast<const T*>(vr + 16);
   }
 }
 
-template <int D>
-__device__ __forceinline__ void fp8_to_ops(const Fp8Frags<D>& f, Ops<D, kKvFp8>& o) {
+// Loaded fragments in compute form.
+template <int D, int KV>
+__device__ __forceinline__ KOps<D, KV> k_ops(const Frags<D, KV>& f) {
+  if constexpr (KV == kKvFp8) {
+    KOps<D, KV> o;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int j = 0; j < D / 32; ++j) o.k[t][j] = fp8x8_to_bf16x8(f.k[t][j]);
+      for (int j = 0; j < D / 32; ++j) o.k[t][j] = fp8x8_to_bf16x8(f.k[t][j]);
+    return o;
+  } else {
+    return f;
+  }
+}
+template <int D, int KV>
+__device__ __forceinline__ VOps<D, KV> v_ops(const Frags<D, KV>& f) {
+  if constexpr (KV == kKvFp8) {
+    VOps<D, KV> o;
 #pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt) o.v[dt][0] = fp8x8_to_bf16x8(f.v[dt][0]);
+    for (int dt = 0; dt < D / 16; ++dt) o.v[dt][0] = fp8x8_to_bf16x8(f.v[dt][0]);
+    return o;
+  } else {
+    return f;
+  }
 }
 
 // Zero the V^T operands of tokens past `valid` in this lane's block, so
 // unused slots of a partial block never reach the value product.
 template <int D, int KV>
-__device__ __forceinline__ void mask_v(Ops<D, KV>& o, int lq, int valid0, int valid1) {
+__device__ __forceinline__ void mask_v(VOps<D, KV>& o, int lq, int valid0, int valid1) {
   const int valid = lq >= 2 ? valid1 : valid0;
   const int slot0 = 8 * (lq & 1);
 #pragma unroll
@@ -359,16 +432,18 @@ __device__ __forceinline__ QFrag<D, KV> q_from_lds(const unsigned char* qlds, in
   return qf;
 }
 
-// kWide: the pair applies to every row of the tile (rows past the unit's
-// end hold zero queries and are never written) and only a missing second
-// block (pi.v1 == 0) is masked, by a reference of +inf for its half of the
-// lanes: no branch, so the compiler interleaves consecutive tiles.
-template <int D, int KV, bool kWide = false>
-__device__ __forceinline__ void tile_step(const Ops<D, KV>& f, const QFrag<D, KV>& qfr, RowState<D>& st,
-                                          const PairInfo& pi, int r, int ln, int lq) {
-  using O = Ops<D, KV>;
+// One pair against one row tile, in three parts: the scores of its tokens
+// (S^T = K Q^T), their probabilities, and the value product (O^T += V^T P^T).
+struct Scores {
+  f32x4 acc[2];
+};
+
+template <int D, int KV>
+__device__ __forceinline__ Scores tile_scores(const KOps<D, KV>& f, const QFrag<D, KV>& qfr) {
+  using O = KOps<D, KV>;
   const auto& qf = qfr.q;
-  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  Scores s = {{{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}};
+  auto& acc = s.acc;
   if constexpr (O::f32) {
 #pragma unroll
     for (int j = 0; j < O::kk; ++j)
@@ -387,6 +462,31 @@ __device__ __forceinline__ void tile_step(const Ops<D, KV>& f, const QFrag<D, KV
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.k[t][j]),
                                                          __builtin_bit_cast(bf16x8, qf[j]), acc[t], 0, 0, 0);
   }
+  return s;
+}
+
+// The probabilities as the value product's operand: bf16 (fp8 caches: times
+// the V scale), or fp32 for fp32 caches.
+template <int KV>
+struct Probs {
+  float p[8];
+};
+template <>
+struct Probs<kKvBf16> {
+  bf16x8 p;
+};
+template <>
+struct Probs<kKvFp8> {
+  bf16x8 p;
+};
+
+// kWide: the pair applies to every row of the tile (rows past the unit's
+// end hold zero queries and are never written) and only a missing second
+// block (pi.v1 == 0) is masked, by a reference of +inf for its half of the
+// lanes: no branch, so the compiler interleaves consecutive tiles.
+template <int D, int KV, bool kWide = false>
+__device__ __forceinline__ Probs<KV> tile_probs(const Scores& s, RowState<D>& st, const PairInfo& pi, int r, int ln,
+                                                int lq) {
   // Lane (ln, lq) holds row 16r + ln, tokens 8lq + 4t + i of the pair: all in
   // block lq >> 1, at slots 8(lq & 1) + 4t + i.
   const bool hi = lq >= 2;
@@ -400,7 +500,7 @@ __device__ __forceinline__ void tile_step(const Ops<D, KV>& f, const QFrag<D, KV
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[4 * t + i] = __builtin_fmaf(acc[t][i], sc, -mref);
+    for (int i = 0; i < 4; ++i) x[4 * t + i] = __builtin_fmaf(s.acc[t][i], sc, -mref);
   const int row = 16 * r + ln;
   const int valid = hi ? pi.v1 : pi.v0;
   const int ra = hi ? pi.a1 : pi.a0, re = hi ? pi.e1 : pi.e0;
@@ -419,9 +519,28 @@ __device__ __forceinline__ void tile_step(const Ops<D, KV>& f, const QFrag<D, KV
 #pragma unroll
   for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(x[i]);
   st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-  if constexpr (O::f32) {
+  Probs<KV> out;
+  if constexpr (KV == kKvF32) {
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) {
+    for (int i = 0; i < 8; ++i) out.p[i] = p[i];
+  } else {
+    const float vs = hi ? pi.vs1 : pi.vs0;
+    float pv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pv[i] = (KV == kKvFp8) ? p[i] * vs : p[i];
+    const uint4 pb = {pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]), pack_bf16x2(pv[4], pv[5]),
+                      pack_bf16x2(pv[6], pv[7])};
+    out.p = __builtin_bit_cast(bf16x8, pb);
+  }
+  return out;
+}
+
+template <int D, int KV>
+__device__ __forceinline__ void tile_values(const VOps<D, KV>& f, const Probs<KV>& pr, RowState<D>& st) {
+  const auto& p = pr.p;
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt) {
+    if constexpr (KV == kKvF32) {
       const f32x4 a0 = f.v[dt][0], a1 = f.v[dt][1];
       f32x4 o = st.o[dt];
       o = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, p[0], o, 0, 0, 0);
@@ -433,25 +552,15 @@ __device__ __forceinline__ void tile_step(const Ops<D, KV>& f, const QFrag<D, KV
       o = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, p[6], o, 0, 0, 0);
       o = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, p[7], o, 0, 0, 0);
       st.o[dt] = o;
+    } else {
+      st.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.v[dt][0]), p, st.o[dt], 0, 0, 0);
     }
-  } else {
-    const float vs = hi ? pi.vs1 : pi.vs0;
-    float pv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) pv[i] = (KV == kKvFp8) ? p[i] * vs : p[i];
-    const uint4 pb = {pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]), pack_bf16x2(pv[4], pv[5]),
-                      pack_bf16x2(pv[6], pv[7])};
-    const bf16x8 pbf = __builtin_bit_cast(bf16x8, pb);
-#pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt)
-      st.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.v[dt][0]), pbf, st.o[dt], 0,
-                                                        0, 0);
   }
 }
 
-// ---- wide units: block pairs shared by the four waves through LDS --------
+// ---- wide units: block pairs shared by the eight waves through LDS -------
 // A pair's operands are kChunks 16-byte fragments per lane (K: tile t, slice
-// j; then V: dim tile dt). Each wave loads a quarter of them (the
+// j; then V: dim tile dt). Each wave loads an eighth of them (the
 // fragments of all 64 lanes, from the addresses load_pair reads) into
 // registers ahead of use, stores them to an LDS stage -- chunk c holds
 // fragment c of every lane, lane i at byte 16 i -- and after a barrier every
@@ -482,18 +591,18 @@ __device__ __forceinline__ const unsigned char* frag_src(int c, const unsigned c
 }
 
 // (A vector value rather than an array, so that it stays in registers.)
-// fp8 caches hold the raw codes (8 bytes per fragment) until the quarter is
+// fp8 caches hold the raw codes (8 bytes per fragment) until the slice is
 // stored, converted, to the stage.
 template <int D, int KV>
-struct Quarter {
+struct Slice {
   static constexpr int kWords = KV == kKvFp8 ? 2 : 4;  // dwords per fragment
   typedef unsigned int V __attribute__((ext_vector_type(kWords * Stage<D, KV>::kPerWave)));
   V v;
 };
 
-// This wave's quarter of pair (id0, id1).
+// This wave's slice of pair (id0, id1).
 template <int D, int KV>
-__device__ __forceinline__ void load_quarter(Quarter<D, KV>& q, int id0, int id1, const unsigned char* kbase,
+__device__ __forceinline__ void load_slice(Slice<D, KV>& q, int id0, int id1, const unsigned char* kbase,
                                              const unsigned char* vbase, size_t blk_stride, int wave, int ln, int lq) {
   using S = Stage<D, KV>;
   const unsigned char* kb0 = kbase + id0 * blk_stride;
@@ -518,7 +627,7 @@ __device__ __forceinline__ void load_quarter(Quarter<D, KV>& q, int id0, int id1
 }
 
 template <int D, int KV>
-__device__ __forceinline__ void store_quarter(const Quarter<D, KV>& q, unsigned char* stage, int wave, int lane) {
+__device__ __forceinline__ void store_slice(const Slice<D, KV>& q, unsigned char* stage, int wave, int lane) {
 #pragma unroll
   for (int i = 0; i < Stage<D, KV>::kPerWave; ++i) {
     uint4 w;
@@ -543,11 +652,17 @@ __device__ __forceinline__ void read_stage(Ops<D, KV>& o, const unsigned char* s
 
 // Per-lane view of up to 64 block entries of a unit: lane i holds entry i.
 struct Window {
-  int id;     // physical block id (clamped into the pool)
-  int valid;  // valid tokens (0: skip)
-  int a, e;   // rows [a, e)
+  int id;      // physical block id (clamped into the pool)
+  uint32_t w;  // rows [a, e) and valid tokens (0: skip), packed by win_word
   float ks, vs;
 };
+
+__device__ __forceinline__ uint32_t win_word(int a, int e, int valid) {
+  return static_cast<uint32_t>(a) | (static_cast<uint32_t>(e - 1) << 6) | (static_cast<uint32_t>(valid) << 12);
+}
+__device__ __forceinline__ int win_a(uint32_t w) { return w & 63; }
+__device__ __forceinline__ int win_e(uint32_t w) { return ((w >> 6) & 63) + 1; }
+__device__ __forceinline__ int win_valid(uint32_t w) { return w >> 12; }
 
 __device__ __forceinline__ int ent_r0(uint32_t inf) { return inf & 63; }
 __device__ __forceinline__ int ent_r1(uint32_t inf) { return ((inf >> 6) & 63) + 1; }
@@ -555,37 +670,107 @@ __device__ __forceinline__ int ent_valid(uint32_t inf) { return ((inf >> 12) & 1
 
 // Loads of pair pp of a window (n entries) into f.
 template <int D, int KV>
+__device__ __forceinline__ void issue_k(Frags<D, KV>& f, const Window& win, int n, int pp, const unsigned char* kbase,
+                                        size_t blk_stride, int ln, int lq) {
+  const int id0 = rl(win.id, 2 * pp);
+  const int id1 = 2 * pp + 1 < n ? rl(win.id, 2 * pp + 1) : id0;
+  load_k<D, KV>(f, kbase + id0 * blk_stride, kbase + id1 * blk_stride, ln, lq);
+}
+template <int D, int KV>
+__device__ __forceinline__ void issue_v(Frags<D, KV>& f, const Window& win, int n, int pp, const unsigned char* vbase,
+                                        size_t blk_stride, int ln, int lq) {
+  const int id0 = rl(win.id, 2 * pp);
+  const int id1 = 2 * pp + 1 < n ? rl(win.id, 2 * pp + 1) : id0;
+  load_v<D, KV>(f, vbase + id0 * blk_stride, vbase + id1 * blk_stride, ln, lq);
+}
+template <int D, int KV>
 __device__ __forceinline__ void issue_pair(Frags<D, KV>& f, const Window& win, int n, int pp,
                                            const unsigned char* kbase, const unsigned char* vbase, size_t blk_stride,
-                                           int ln, int lq, bool standin = false) {
-  const int i0 = 2 * pp, i1 = 2 * pp + 1;
-  const int id0 = rl(win.id, i0);
-  const int id1 = i1 < n ? rl(win.id, i1) : id0;
-  load_pair<D, KV>(f, kbase + id0 * blk_stride, kbase + id1 * blk_stride, vbase + id0 * blk_stride,
-                   vbase + id1 * blk_stride, ln, lq, standin);
+                                           int ln, int lq) {
+  issue_k<D, KV>(f, win, n, pp, kbase, blk_stride, ln, lq);
+  issue_v<D, KV>(f, win, n, pp, vbase, blk_stride, ln, lq);
 }
 
-// Runs every pair of a window (n entries) through the unit's row tiles
-// (rows outside a block's range are masked); pairs w, w + 4, ... belong to
-// wave w. The next pair's loads are issued before the current pair is
-// computed; the wave's first pair has been issued into fa by the caller.
+// How the waves of a workgroup share a narrow unit: a wave holds the states
+// of kNt row tiles (NarrowTiles), so units of more tiles split the waves
+// into groups by tile, and the waves of a group take its block pairs in
+// turn. A pair with rows of two groups is read by both (from L2 the second
+// time).
+template <int KV>
+struct NarrowTiles {
+  static constexpr int value = KV == kKvF32 ? 1 : 2;  // row tiles per wave
+};
+
+struct Split {
+  int ng;    // groups
+  int n;     // waves of this wave's group
+  int grp;   // the group: row tiles grp * kNt .. + kNt
+  int sub;   // this wave's place in it: pairs sub, sub + n, ...
+  int n0;    // two groups: waves of the first
+};
+
+// First wave of group g, and its waves (ng = 1: all; two groups: n0 and the
+// rest; four: two each).
+__device__ __forceinline__ int group_first(const Split& w, int g) { return w.ng == 2 ? (g ? w.n0 : 0) : g * 2; }
+__device__ __forceinline__ int group_waves(const Split& w, int g) {
+  return w.ng == 1 ? kWaves : (w.ng == 2 ? (g ? kWaves - w.n0 : w.n0) : 2);
+}
+
+// n0: the record's share of the first group when there are two (its pairs
+// over all of the unit's).
+template <int KV>
+__device__ __forceinline__ Split split_waves(int nrows, int n0, int wave) {
+  constexpr int kNt = NarrowTiles<KV>::value;
+  Split w;
+  w.ng = nrows <= 16 * kNt ? 1 : (nrows <= 32 * kNt ? 2 : 4);
+  w.n0 = n0;
+  w.grp = w.ng == 1 ? 0 : (w.ng == 2 ? (wave >= n0 ? 1 : 0) : wave >> 1);
+  w.n = group_waves(w, w.grp);
+  w.sub = wave - group_first(w, w.grp);
+  return w;
+}
+
+// The pairs of a window (n entries) that hold rows of group grp: bit 2 i
+// set for pair i. drop_pairs takes the first k of them away.
+template <int KV>
+__device__ __forceinline__ uint64_t group_pairs(const Window& win, int n, int grp, int lane) {
+  constexpr int kRows = 16 * NarrowTiles<KV>::value;
+  const int r0 = grp * kRows;
+  const bool in = lane < n && win_a(win.w) < r0 + kRows && win_e(win.w) > r0;
+  const uint64_t e = __builtin_amdgcn_ballot_w64(in);
+  return (e | (e >> 1)) & 0x5555555555555555ull;
+}
+__device__ __forceinline__ uint64_t drop_pairs(uint64_t m, int k) {
+  for (int i = 0; i < k; ++i) m &= m - 1;
+  return m;
+}
+__device__ __forceinline__ int first_pair(uint64_t m) { return static_cast<int>(__builtin_ctzll(m)) >> 1; }
+
+// Runs every pair of a window (n entries) through this wave's row tiles
+// (rows outside a block's range are masked): the pairs set in `pairs` (its
+// share starts at the first, then every ws.n-th). The first has been issued
+// into fa by the caller. One pair of load registers, refilled with the next
+// pair when it has been used (the eight waves of a workgroup keep up to
+// 128 KB in flight, and the other wave of the SIMD computes meanwhile).
 template <int D, int KV>
-__device__ __forceinline__ void run_window(const Window& win, int n, int nt, const unsigned char* kbase,
-                                           const unsigned char* vbase, size_t blk_stride, float sc,
-                                           const unsigned char* qlds, RowState<D> (&st)[kTiles],
-                                           Frags<D, KV>& fa, int wave, int ln, int lq) {
-  const int np = (n + 1) >> 1;
-  if (wave >= np) return;
+__device__ __forceinline__ void run_window(const Window& win, int n, int nrows, const Split& ws,
+                                           const unsigned char* kbase, const unsigned char* vbase, size_t blk_stride,
+                                           float sc, const unsigned char* qlds,
+                                           RowState<D> (&st)[NarrowTiles<KV>::value], Frags<D, KV>& fa,
+                                           uint64_t pairs, int ln, int lq) {
+  constexpr int kNt = NarrowTiles<KV>::value;
+  if (pairs == 0) return;
   auto info = [&](int pp) {
     PairInfo pi;
     const int i0 = 2 * pp, i1 = 2 * pp + 1;
     const bool has1 = i1 < n;
-    pi.v0 = rl(win.valid, i0);
-    pi.v1 = has1 ? rl(win.valid, i1) : 0;
-    pi.a0 = rl(win.a, i0);
-    pi.e0 = rl(win.e, i0);
-    pi.a1 = has1 ? rl(win.a, i1) : 0;
-    pi.e1 = has1 ? rl(win.e, i1) : 0;
+    const uint32_t w0 = rl(win.w, i0), w1 = rl(win.w, i1 & 63);
+    pi.v0 = win_valid(w0);
+    pi.v1 = has1 ? win_valid(w1) : 0;
+    pi.a0 = win_a(w0);
+    pi.e0 = win_e(w0);
+    pi.a1 = has1 ? win_a(w1) : 0;
+    pi.e1 = has1 ? win_e(w1) : 0;
     pi.ks0 = sc;
     pi.ks1 = sc;
     pi.vs0 = 1.f;
@@ -598,8 +783,9 @@ __device__ __forceinline__ void run_window(const Window& win, int n, int nt, con
     }
     return pi;
   };
-  auto tiles = [&](Ops<D, KV>& o, const PairInfo& pi) {
-    if (pi.v0 < kTok || pi.v1 < kTok) mask_v<D, KV>(o, lq, pi.v0, pi.v1);
+  for (;;) {
+    const PairInfo pi = info(first_pair(pairs));
+    pairs = drop_pairs(pairs, ws.n);
     // Row tiles the pair's valid blocks apply to.
     int lo = kMaxRows, hi = 0;
     if (pi.v0 > 0) {
@@ -610,50 +796,52 @@ __device__ __forceinline__ void run_window(const Window& win, int n, int nt, con
       lo = lo < pi.a1 ? lo : pi.a1;
       hi = hi > pi.e1 ? hi : pi.e1;
     }
-    const int t0 = lo >> 4, t1 = (hi - 1) >> 4;
+    bool act[kNt];
 #pragma unroll
-    for (int r = 0; r < kTiles; ++r)
-      if (r < nt && r >= t0 && r <= t1) tile_step<D, KV>(o, q_from_lds<D, KV>(qlds, r, ln, lq), st[r], pi, r, ln, lq);
-  };
-  auto compute = [&](Frags<D, KV>& f, int pp) {
-    const PairInfo pi = info(pp);
-    if (pi.v0 <= 0 && pi.v1 <= 0) return;
-    if constexpr (KV == kKvFp8) {
-      Ops<D, KV> o;
-      fp8_to_ops<D>(f, o);
-      tiles(o, pi);
-    } else {
-      tiles(f, pi);
+    for (int i = 0; i < kNt; ++i) {
+      const int r = ws.grp * kNt + i;
+      act[i] = 16 * r < nrows && 16 * r < hi && 16 * r + 16 > lo;
     }
-  };
-  auto issue = [&](Frags<D, KV>& f, int pp, bool standin) {
-    issue_pair<D, KV>(f, win, n, pp, kbase, vbase, blk_stride, ln, lq, standin);
-  };
-  // The next pair's loads are always issued (constant wait counts); past the
-  // wave's last pair they are stand-ins that all read the first 16 bytes of
-  // the pair just loaded (a cache hit), so later waits on them are short.
-  Frags<D, KV> fb;
-  int pp = wave;
-  for (;;) {
-    int pn = pp + kWaves;
-    bool more = pn < np;
-    issue(fb, more ? pn : pp, !more);
-    compute(fa, pp);
-    if (!more) break;
-    pp = pn;
-    pn = pp + kWaves;
-    more = pn < np;
-    issue(fa, more ? pn : pp, !more);
-    compute(fb, pp);
-    if (!more) break;
-    pp = pn;
+    if constexpr (KV == kKvFp8) {
+      // All tiles' scores, then all value products, so that only one of the
+      // converted operands is held at a time.
+      Scores s[kNt];
+      {
+        const KOps<D, KV> k = k_ops<D, KV>(fa);
+#pragma unroll
+        for (int i = 0; i < kNt; ++i)
+          if (act[i]) s[i] = tile_scores<D, KV>(k, q_from_lds<D, KV>(qlds, ws.grp * kNt + i, ln, lq));
+      }
+      if (pairs != 0) issue_k<D, KV>(fa, win, n, first_pair(pairs), kbase, blk_stride, ln, lq);
+      Probs<KV> pr[kNt];
+#pragma unroll
+      for (int i = 0; i < kNt; ++i)
+        if (act[i]) pr[i] = tile_probs<D, KV>(s[i], st[i], pi, ws.grp * kNt + i, ln, lq);
+      VOps<D, KV> v = v_ops<D, KV>(fa);
+      if (pi.v0 < kTok || pi.v1 < kTok) mask_v<D, KV>(v, lq, pi.v0, pi.v1);
+#pragma unroll
+      for (int i = 0; i < kNt; ++i)
+        if (act[i]) tile_values<D, KV>(v, pr[i], st[i]);
+      if (pairs == 0) break;
+      issue_v<D, KV>(fa, win, n, first_pair(pairs), vbase, blk_stride, ln, lq);
+    } else {
+      if (pi.v0 < kTok || pi.v1 < kTok) mask_v<D, KV>(fa, lq, pi.v0, pi.v1);
+#pragma unroll
+      for (int i = 0; i < kNt; ++i)
+        if (act[i]) {
+          const int r = ws.grp * kNt + i;
+          const Scores s = tile_scores<D, KV>(fa, q_from_lds<D, KV>(qlds, r, ln, lq));
+          tile_values<D, KV>(fa, tile_probs<D, KV>(s, st[i], pi, r, ln, lq), st[i]);
+        }
+      if (pairs == 0) break;
+      issue_pair<D, KV>(fa, win, n, first_pair(pairs), kbase, vbase, blk_stride, ln, lq);
+    }
   }
 }
 
-// A unit's record as held by a wave: header fields (every lane holds the
-// same value; made uniform with readfirstlane where used, so that a record
-// fetched ahead of time is not waited for early) and, per lane, beam `lane`
-// (lane < 16) and entry `lane`.
+// A unit's record as held by a wave: the header in scalar registers (read
+// through the scalar cache; the records are not written while the kernel
+// runs) and, per lane, beam `lane` and entry `lane`.
 struct UnitRegs {
   int kvh, nrows, nstatic, nent, prow0, next, mode, nstatic2;
   int beam_l;
@@ -670,19 +858,21 @@ __device__ __forceinline__ void load_window2(const UnitRec* recs, int idx, int l
 
 __device__ __forceinline__ int rfl(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef const i32x8 __attribute__((address_space(4))) * ConstI32x8;
+
 __device__ __forceinline__ UnitRegs load_unit(const UnitRec* recs, int idx, int lane) {
   const UnitRec* r = recs + idx;
   UnitRegs u;
-  const int4 h0 = *reinterpret_cast<const int4*>(&r->kvh);
-  const int4 h1 = *reinterpret_cast<const int4*>(&r->prow0);
-  u.kvh = h0.x;
-  u.nrows = h0.y;
-  u.nstatic = h0.z;
-  u.nent = h0.w;
-  u.prow0 = h1.x;
-  u.next = h1.y;
-  u.mode = h1.z;
-  u.nstatic2 = h1.w;
+  const i32x8 h = *(ConstI32x8)(reinterpret_cast<uintptr_t>(&r->kvh));
+  u.kvh = h[0];
+  u.nrows = h[1];
+  u.nstatic = h[2];
+  u.nent = h[3];
+  u.prow0 = h[4];
+  u.next = h[5];
+  u.mode = h[6];
+  u.nstatic2 = h[7];
   u.beam_l = r->beams[lane];
   u.ent_id = r->ent_id[lane];
   u.ent_inf = r->ent_info[lane];
@@ -759,13 +949,16 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   using G = Geo<D, KV>;
   using Q = QLds<D, KV>;
   // LDS: the current unit's query rows, and the end-of-unit combine area
-  // where each wave publishes the states of the row tiles other waves
-  // combine (3 x 4 (wave, tile) slots).
-  // Wide units (bf16) use the area after the query rows for their pair
-  // stages instead.
-  constexpr int kCombBytes = kWaves * (kTiles - 1) * G::comb_floats * 4;
-  constexpr int kStageBytes = KV != kKvF32 ? 2 * Stage<D, KV>::bytes : 0;
-  constexpr int kAreaBytes = kCombBytes > kStageBytes ? kCombBytes : kStageBytes;
+  // where every wave publishes its row tiles' states.
+  // Wide units (bf16 and fp8) use the area after the query rows for their
+  // pair stages instead.
+  constexpr int kNt = NarrowTiles<KV>::value;
+  constexpr int kGroups = kTiles / kNt;  // wave groups of the largest narrow unit
+  constexpr int kCombBytes = kWaves * kNt * G::comb_floats * 4;
+  constexpr int kStageBytes = KV != kKvF32 ? 2 * kStepPairs * Stage<D, KV>::bytes : 0;
+  constexpr int kFoldBytes = KV != kKvF32 ? kWaves * (64 * (D + 8)) : 0;  // wide units' halves: a tile per wave
+  constexpr int kAreaBytes = kCombBytes > kStageBytes ? (kCombBytes > kFoldBytes ? kCombBytes : kFoldBytes)
+                                                      : (kStageBytes > kFoldBytes ? kStageBytes : kFoldBytes);
   // Narrow units with a second window park its entries (per lane: block id
   // and info word; every wave writes the same values) until the first one
   // is done, instead of holding two more registers through the pair loop.
@@ -778,25 +971,32 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   uint2* win2_lds = reinterpret_cast<uint2*>(lds + Q::bytes + kAreaBytes);
   int* votes = reinterpret_cast<int*>(lds + Q::bytes + kAreaBytes + kWin2Bytes);
 
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const int lane = tid & 63;
-  const int ln = lane & 15;
-  const int lq = lane >> 4;
+  const int wave = rfl(static_cast<int>(threadIdx.x) >> 6);
+  // The thread's coordinates, opaque to the optimiser once per unit: lane
+  // address arithmetic hoisted out of the unit loop as constants of the
+  // whole kernel would be spilled to scratch memory (244 bytes per thread,
+  // written by every workgroup of every launch).
+  int tid, lane, ln, lq;
+  auto coords = [&]() {
+    tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    ln = lane & 15;
+    lq = lane >> 4;
+  };
+  coords();
   const size_t blk_stride = static_cast<size_t>(p.hkv) * G::blk_bytes;
   const bool paged = p.recs == nullptr;
   const float sc_w = p.scale_log2;
   const float sc = p.scale_log2;
-  auto comb_slot = [&](int w, int r) {  // (wave w, tile r != w)
-    return comb + (w * (kTiles - 1) + (r < w ? r : r - 1)) * G::comb_floats;
-  };
+  auto comb_slot = [&](int w, int i) { return comb + (w * kNt + i) * G::comb_floats; };  // (wave, its tile)
 
   // ---- first unit -----------------------------------------------------------
   int rec_idx;
   UnitRegs u;
   int paged_b = 0, paged_split = 0;
   if (!paged) {
-    rec_idx = static_cast<int>(blockIdx.x);
+    rec_idx = blockIdx.x;
     u = load_unit(p.recs, rec_idx, lane);
   } else {
     // Paged path: unit = (beam, KV head, split) from the workgroup id, one
@@ -811,7 +1011,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     u.nent = 0;
     u.prow0 = 0;
     u.next = -1;
-    u.mode = kModeNarrow;
+    u.mode = kModeNarrow | (kWaves / 2) << 8;
     u.beam_l = paged_b;
     u.ent_id = 0;
     u.ent_inf = 0;
@@ -821,22 +1021,34 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   QRegs<D, KV> qr;
   load_q<D, KV>(p, u, qr, tid);
   Frags<D, KV> fa;
-  bool fa_ready = false;  // the unit's first pair, lengths and next record are in flight
+  bool fa_ready = false;  // the unit's first pair and lengths are in flight
+  // fp32 at D = 128: a pair is 128 registers, too many to hold while the
+  // previous unit combines.
+  constexpr bool kEarlyPair = KV != kKvF32 || D < 128;
   int ext_len = 0, ext_build = 0;  // live / extension lanes: live and build-time length
   UnitRegs nu;
   // Hand-over to unit n: a narrow unit's query rows, first pair and lengths
   // go out before this unit's combine. Every path assigns the carried
   // registers, so their previous contents are dead while a unit runs.
   auto handover = [&](const UnitRegs& n) {
-    if (rfl(n.mode) == kModeNarrow) {
+    if ((n.mode & 0xff) == kModeNarrow) {
       load_q<D, KV>(p, n, qr, tid);
+      if (!kEarlyPair) {
+        fa_ready = false;
+        return;
+      }
       const int nn = rfl(n.nstatic), nkvh = rfl(n.kvh);
       Window nw;
       nw.id = n.ent_id;
-      issue_pair<D, KV>(fa, nw, nn > 0 ? nn : 1, wave < ((nn + 1) >> 1) ? wave : 0,
-                        static_cast<const unsigned char*>(p.k_cache) + nkvh * G::blk_bytes,
-                        static_cast<const unsigned char*>(p.v_cache) + nkvh * G::blk_bytes, blk_stride, ln, lq,
-                        wave >= ((nn + 1) >> 1));
+      const Split nws = split_waves<KV>(n.nrows, n.mode >> 8, wave);
+      nw.w = win_word(ent_r0(n.ent_inf), ent_r1(n.ent_inf), 0);
+      const uint64_t npairs = drop_pairs(group_pairs<KV>(nw, nn, nws.grp, lane), nws.sub);
+      if (npairs != 0)
+        issue_pair<D, KV>(fa, nw, nn, first_pair(npairs),
+                          static_cast<const unsigned char*>(p.k_cache) + nkvh * G::blk_bytes,
+                          static_cast<const unsigned char*>(p.v_cache) + nkvh * G::blk_bytes, blk_stride, ln, lq);
+      else
+        fa = Frags<D, KV>{};
       issue_live(p, n, lane, &ext_len, &ext_build);
     } else {
       qr = QRegs<D, KV>{};
@@ -848,6 +1060,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   };
 
   for (;;) {
+    coords();
     TTS_PROF_MARK(0, rec_idx);
     const int kvh = rfl(u.kvh), nrows = rfl(u.nrows), nent = rfl(u.nent), prow0 = rfl(u.prow0),
               unext = rfl(u.next);
@@ -856,17 +1069,26 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     const unsigned char* vbase = static_cast<const unsigned char*>(p.v_cache) + kvh * G::blk_bytes;
 
     if constexpr (KV != kKvF32) {
-      if (rfl(u.mode) == kModeWide) {
-        // ---- wide unit: wave w owns row tiles w, w + 4, ...; every block
-        // pair is copied to an LDS stage once and read by all four waves ---
+      if ((u.mode & 0xff) == kModeWide) {
+        // ---- wide unit: every block pair is copied to an LDS stage once and
+        // read from there. Up to eight row tiles: four waves hold all of them
+        // (wave w tiles w % 4 and w % 4 + 4) and each half of the workgroup
+        // takes one pair of every step; the halves' states are added at the
+        // end. (LDS reads bound this loop: 128 bytes a clock, 16 KB per wave
+        // and pair. With two tiles per wave a pair is read four times
+        // instead of eight.) More tiles: wave w holds tiles w and w + 8 and
+        // computes every pair.
         using SG = Stage<D, KV>;
         const int nst = rfl(u.nstatic);
+        const bool halves = nt <= kWaves;
+        const int half = halves ? wave >> 2 : 0;
+        const int tile0 = halves ? wave & 3 : wave, tstep = halves ? 4 : kWaves;
         nu.nrows = 0;
         if (unext >= 0) nu = load_unit(p.recs, unext, lane);
         QFrag<D, KV> qw[kWideTiles];
 #pragma unroll
         for (int i = 0; i < kWideTiles; ++i) {
-          const int row = 16 * (wave + kWaves * i) + ln;
+          const int row = 16 * (tile0 + tstep * i) + ln;
           const bool ok = row < nrows;
           const int b = __shfl(u.beam_l, ok ? row / p.g : 0);
           const int qh = kvh * p.g + (ok ? row % p.g : 0);
@@ -877,7 +1099,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         }
         unsigned char* stages = lds + Q::bytes;
         const int np = (nst + 1) >> 1;
-        const int tpw = (nt + kWaves - 1) / kWaves;
+        const int nsteps = (np + kStepPairs - 1) / kStepPairs;
+        // Row tiles of this wave: a wave with none still stages its share.
+        const int wtiles = nt > tile0 + tstep ? 2 : (nt > tile0 ? 1 : 0);
         // A wide unit has up to kMaxUnitEntries blocks, numbered across its
         // two windows: entry i < 64 in lane i of ent_id, entry 64 + i in lane
         // i of ent_id2. Entries (e0, e1) and block ids of pair pp; a pair
@@ -920,102 +1144,70 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
             st[i].l = 0.f;
             st[i].seen = kNegInf;
           }
-          // Two quarters. bf16: each step first sends the next pair's loads
-          // into the other quarter. fp8 (quarters of half the size): each
-          // quarter is refilled with the pair two ahead as soon as it is
-          // staged, so its loads are in flight for about two steps (faster
-          // for fp8, slower for bf16 as compiled, where the wait counts of
-          // alternate steps cover both quarters).
-          constexpr bool kRefill = KV == kKvFp8;
-          Quarter<D, KV> qa, qb;
-          // fp8: the pair's block scales (K of block 0, 1; V of block 0, 1).
-          auto scales = [&]() {
-            if constexpr (KV == kKvFp8) {
-              const float ks = e0 < kMaxEntries ? ksl : ksl2, vs = e0 < kMaxEntries ? vsl : vsl2;
-              const int i0 = e0 & (kMaxEntries - 1), i1 = e1 & (kMaxEntries - 1);
-              return f32x4{rlf(ks, i0), rlf(ks, i1), rlf(vs, i0), rlf(vs, i1)};
-            } else {
-              return f32x4{1.f, 1.f, 1.f, 1.f};
+          // This wave's slices of the step's pairs: refilled with the next
+          // step's as soon as they are staged, so the loads are in flight for
+          // a whole step.
+          Slice<D, KV> cur[kStepPairs];
+          auto load_step = [&](int sidx) {
+#pragma unroll
+            for (int h = 0; h < kStepPairs; ++h) {
+              pair_ids(kStepPairs * sidx + h);
+              load_slice<D, KV>(cur[h], id0, id1, kbase, vbase, blk_stride, wave, ln, lq);
             }
           };
-          pair_ids(0);
-          load_quarter<D, KV>(qa, id0, id1, kbase, vbase, blk_stride, wave, ln, lq);
-          if constexpr (kRefill) {
-            pair_ids(1);
-            load_quarter<D, KV>(qb, id0, id1, kbase, vbase, blk_stride, wave, ln, lq);
-          }
+          load_step(0);
           __syncthreads();  // every wave is done with the stage area (previous unit or attempt)
-          // tpw_c: the tiles per wave as a constant of this copy of the
-          // loop, or 0 for the count read at run time.
-          auto step = [&](auto tpw_c, Quarter<D, KV>& cur, Quarter<D, KV>& nxt, int pp) {
-            unsigned char* stage = stages + (pp & 1) * SG::bytes;
-            if constexpr (kRefill) {
-              store_quarter<D, KV>(cur, stage, wave, lane);
-              pair_ids(pp + 2);
-              load_quarter<D, KV>(cur, id0, id1, kbase, vbase, blk_stride, wave, ln, lq);
-            } else {
-              pair_ids(pp + 1);
-              load_quarter<D, KV>(nxt, id0, id1, kbase, vbase, blk_stride, wave, ln, lq);
-              store_quarter<D, KV>(cur, stage, wave, lane);
-            }
-            pair_ids(pp);
-            const f32x4 cs = scales();
-            __syncthreads();  // the whole pair is in the stage
-            Ops<D, KV> o;
-            read_stage<D, KV>(o, stage, lane);
-            // fp8: the compiler's interleaving strategy for small matrix
-            // products with LDS reads (long chain -1.5%; for bf16 it
-            // measured within noise).
-            if constexpr (KV == kKvFp8) __builtin_amdgcn_iglp_opt(1);
-            PairInfo pi;
-            pi.v0 = kTok;
-            pi.v1 = 2 * pp + 1 < nst ? kTok : 0;
-            pi.a0 = pi.a1 = 0;
-            pi.e0 = pi.e1 = nrows;
-            pi.ks0 = sc_w * cs.x;
-            pi.ks1 = sc_w * cs.y;
-            pi.vs0 = cs.z;
-            pi.vs1 = cs.w;
-            if (pi.v1 == 0) mask_v<D, KV>(o, lq, pi.v0, pi.v1);
-            constexpr int kTpw = decltype(tpw_c)::value;
-            if constexpr (kTpw > 0) {
-#pragma unroll
-              for (int i = 0; i < kTpw; ++i) tile_step<D, KV, true>(o, qw[i], st[i], pi, wave + kWaves * i, ln, lq);
-            } else if (tpw >= kWideTiles) {
-              // The unit's tiles per wave (uniform): one straight-line block
-              // per count, so the compiler interleaves the tiles' products.
-#pragma unroll
-              for (int i = 0; i < kWideTiles; ++i) tile_step<D, KV, true>(o, qw[i], st[i], pi, wave + kWaves * i, ln, lq);
-            } else if (tpw == 2) {
-#pragma unroll
-              for (int i = 0; i < 2; ++i) tile_step<D, KV, true>(o, qw[i], st[i], pi, wave + kWaves * i, ln, lq);
-            } else {
-              tile_step<D, KV, true>(o, qw[0], st[0], pi, wave, ln, lq);
-            }
-          };
+          // kTpw: this wave's row tiles.
           auto run = [&](auto tpw_c) {
-            for (int pp = 0; pp < np; pp += 2) {
-              step(tpw_c, qa, qb, pp);
-              if (pp + 1 >= np) break;
-              step(tpw_c, qb, qa, pp + 1);
+            constexpr int kTpw = decltype(tpw_c)::value;
+            for (int sidx = 0; sidx < nsteps; ++sidx) {
+              unsigned char* stage = stages + (sidx & 1) * kStepPairs * SG::bytes;
+#pragma unroll
+              for (int h = 0; h < kStepPairs; ++h) store_slice<D, KV>(cur[h], stage + h * SG::bytes, wave, lane);
+              load_step(sidx + 1);
+              __syncthreads();  // the step's pairs are in the stage
+              if constexpr (kTpw > 0) {
+                const int h0 = halves ? half : 0, h1 = halves ? half + 1 : kStepPairs;
+#pragma unroll 1
+                for (int h = h0; h < h1; ++h) {
+                  const int pp = kStepPairs * sidx + h;
+                  if (pp >= np) break;  // the last step's missing pair
+                  pair_ids(pp);
+                  PairInfo pi;
+                  pi.v0 = kTok;
+                  pi.v1 = 2 * pp + 1 < nst ? kTok : 0;
+                  pi.a0 = pi.a1 = 0;
+                  pi.e0 = pi.e1 = nrows;
+                  pi.ks0 = pi.ks1 = sc_w;
+                  pi.vs0 = pi.vs1 = 1.f;
+                  if constexpr (KV == kKvFp8) {
+                    const float ks = e0 < kMaxEntries ? ksl : ksl2, vs = e0 < kMaxEntries ? vsl : vsl2;
+                    const int i0 = e0 & (kMaxEntries - 1), i1 = e1 & (kMaxEntries - 1);
+                    pi.ks0 = sc_w * rlf(ks, i0);
+                    pi.ks1 = sc_w * rlf(ks, i1);
+                    pi.vs0 = rlf(vs, i0);
+                    pi.vs1 = rlf(vs, i1);
+                  }
+                  Ops<D, KV> o;
+                  read_stage<D, KV>(o, stage + h * SG::bytes, lane);
+                  if (pi.v1 == 0) mask_v<D, KV>(o, lq, pi.v0, pi.v1);
+#pragma unroll
+                  for (int i = 0; i < kTpw; ++i)
+                    tile_values<D, KV>(o, tile_probs<D, KV, true>(tile_scores<D, KV>(o, qw[i]), st[i], pi, 0, ln, lq),
+                                       st[i]);
+                }
+              }
             }
           };
-          // fp8: one copy of the loop per tiles-per-wave count. In the single
-          // loop the compiler copies the accumulators of the tiles that one
-          // branch updates and another does not at every join (~78 64-bit
-          // moves per pair at three tiles); the copies go away with the
-          // joins (long chain -2%). bf16 keeps the single loop: its per-count
-          // copies measured slower (7b64 +0.5 us, straggler +0.6 us).
-          if constexpr (KV == kKvFp8) {
-            if (tpw >= kWideTiles)
-              run(std::integral_constant<int, kWideTiles>{});
-            else if (tpw == 2)
-              run(std::integral_constant<int, 2>{});
-            else
-              run(std::integral_constant<int, 1>{});
-          } else {
+          // One copy of the loop per tile count: branch-free tile steps, and
+          // no accumulator copies at joins. (Waves of one workgroup run
+          // different copies; every copy meets the same barriers.)
+          if (wtiles == 2)
+            run(std::integral_constant<int, 2>{});
+          else if (wtiles == 1)
+            run(std::integral_constant<int, 1>{});
+          else
             run(std::integral_constant<int, 0>{});
-          }
           if (attempt == 0) TTS_PROF_MARK(1, rec_idx);
           if (attempt > 0) break;
           bool redo = false;
@@ -1026,12 +1218,50 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
             m_exact[i] = mx == kNegInf ? 0.f : mx;
           }
           // The loop holds barriers, so every wave repeats it or none does:
-          // each wave votes, and all four read every vote. (The votes are
+          // each wave votes, and all eight read every vote. (The votes are
           // written again only after the next unit's first barrier.)
           const bool wave_redo = __builtin_amdgcn_ballot_w64(redo) != 0;
           if (lane == 0) votes[wave] = wave_redo ? 1 : 0;
           __syncthreads();
-          if ((votes[0] | votes[1] | votes[2] | votes[3]) == 0) break;
+          int any = 0;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) any |= votes[w];
+          if (any == 0) break;
+        }
+        // Halves: each wave hands one of its tiles to the wave that shares its
+        // rows and adds that wave's other tile: half 0 ends with tile w % 4,
+        // half 1 with w % 4 + 4. (The vote's barrier is past the last read of
+        // the stages.) Lane order, one 16-byte column per 16 dims.
+        if (halves) {
+          auto fold_at = [&](int w) { return comb + w * (16 * (D + 8)); };
+          auto give = [&](RowState<D>& x) {
+            float* c = fold_at(wave);
+#pragma unroll
+            for (int dt = 0; dt < D / 16; ++dt) *reinterpret_cast<f32x4*>(c + 256 * dt + 4 * lane) = x.o[dt];
+            *reinterpret_cast<f32x2*>(c + 16 * D + 2 * lane) = f32x2{x.m, x.l};
+          };
+          auto take = [&](RowState<D>& x) {
+            const float* c = fold_at(wave ^ 4);
+            f32x4 t[D / 16];
+#pragma unroll
+            for (int dt = 0; dt < D / 16; ++dt) t[dt] = *reinterpret_cast<const f32x4*>(c + 256 * dt + 4 * lane);
+            const f32x2 ml = *reinterpret_cast<const f32x2*>(c + 16 * D + 2 * lane);
+            // A half that saw no token of the row must not set the reference.
+            const float l1 = xlane_sum16(x.l), l2 = xlane_sum16(ml.y);
+            const float m1 = l1 > 0.f ? x.m : kNegInf, m2 = l2 > 0.f ? ml.x : kNegInf;
+            const float mx = fmaxf(m1, m2);
+            const float f1 = m1 == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m1 - mx);
+            const float f2 = m2 == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m2 - mx);
+            x.m = mx;
+            x.l = x.l * f1 + ml.y * f2;
+#pragma unroll
+            for (int dt = 0; dt < D / 16; ++dt) x.o[dt] = x.o[dt] * f1 + t[dt] * f2;
+          };
+          if (half == 0 && wtiles == 2) give(st[1]);
+          if (half == 1 && wtiles >= 1) give(st[0]);
+          __syncthreads();
+          if (half == 0 && wtiles >= 1) take(st[0]);
+          if (half == 1 && wtiles == 2) take(st[1]);
         }
         // Each wave writes the partial states of its own rows. The sums and
         // scales of all its tiles first, in straight-line code, so that the
@@ -1047,8 +1277,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         for (int i = 0; i < kWideTiles; ++i) e_[i] = partial_exp<D, KV>(st[i].o);
 #pragma unroll
         for (int i = 0; i < kWideTiles; ++i) {
-          if (wave + kWaves * i >= nt) continue;  // wave-uniform
-          const int row = 16 * (wave + kWaves * i) + ln;
+          if (i >= wtiles || (halves && i != half)) continue;  // wave-uniform
+          const int row = 16 * (tile0 + tstep * i) + ln;
           const int64_t prow = static_cast<int64_t>(kvh) * p.rows_per_head + prow0 + row;
           if (row < nrows) store_partial<D, KV>(p.part_o, p.part_ml, prow, st[i].o, st[i].m, lw_[i], inv_[i], e_[i], lq);
         }
@@ -1068,9 +1298,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     int nstatic = rfl(u.nstatic);
     if (!paged) {
       win.id = u.ent_id;
-      win.a = ent_r0(u.ent_inf);
-      win.e = ent_r1(u.ent_inf);
-      win.valid = lane < nstatic ? ent_valid(u.ent_inf) : 0;
+      win.w = win_word(ent_r0(u.ent_inf), ent_r1(u.ent_inf), lane < nstatic ? ent_valid(u.ent_inf) : 0);
       if (!fa_ready) issue_live(p, u, lane, &ext_len, &ext_build);
     } else {
       const int L = p.seq_lens[paged_b];
@@ -1097,15 +1325,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         }
       }
       win.id = id;
-      win.valid = v;
-      win.a = 0;
-      win.e = nrows;
+      win.w = win_word(0, nrows, v);
       if (__builtin_amdgcn_ballot_w64(bad) != 0) bad_rows = ~0ull;
     }
     win.ks = 1.f;
     win.vs = 1.f;
     if constexpr (KV == kKvFp8) {
-      if (win.valid > 0) {
+      if (win_valid(win.w) > 0) {
         win.ks = p.k_scale[win.id];
         win.vs = p.v_scale[win.id];
       }
@@ -1119,8 +1345,19 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
       load_window2(p.recs, rec_idx, lane, &id2, &inf2);
       win2_lds[lane] = uint2{static_cast<uint32_t>(id2), inf2};
     }
-    if (!fa_ready && wave < ((nstatic + 1) >> 1))
-      issue_pair<D, KV>(fa, win, nstatic, wave, kbase, vbase, blk_stride, ln, lq);
+    const Split ws = split_waves<KV>(nrows, u.mode >> 8, wave);
+    const uint64_t pairs0 = drop_pairs(group_pairs<KV>(win, nstatic, ws.grp, lane), ws.sub);
+    // Waves of each group that are given a pair: those of its first window,
+    // or all (when the unit has more windows).
+    bool wave_has = pairs0 != 0;
+    int nsrc[kGroups];
+#pragma unroll
+    for (int gq = 0; gq < kGroups; ++gq) {
+      const int c = __builtin_popcountll(group_pairs<KV>(win, nstatic, gq, lane)), n = group_waves(ws, gq);
+      nsrc[gq] = c < n ? c : n;
+    }
+    if (!fa_ready && pairs0 != 0)
+      issue_pair<D, KV>(fa, win, nstatic, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
     // The next unit's record: it has this unit's pair loop to arrive.
     nu.nrows = 0;
     if (unext >= 0) nu = load_unit(p.recs, unext, lane);
@@ -1130,26 +1367,26 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
 
     // ---- the unit's blocks with m_ref = 0; again with every row's exact
     // maximum in the rare case that a row's maximum left the safe window ----
-    RowState<D> st[kTiles];
-    float m_exact[kTiles];
+    RowState<D> st[kNt];
+    float m_exact[kNt];
 #pragma unroll
-    for (int r = 0; r < kTiles; ++r) m_exact[r] = 0.f;
+    for (int r = 0; r < kNt; ++r) m_exact[r] = 0.f;
     if (!paged && lane < nstatic && (u.ent_inf & kEntLive)) {
       // The beam's partial last block: it fills up as tokens are appended.
-      const int v = win.valid + (ext_len - ext_build);
-      win.valid = v < 0 ? 0 : (v > kTok ? kTok : v);
+      const int v = win_valid(win.w) + (ext_len - ext_build);
+      win.w = win_word(win_a(win.w), win_e(win.w), v < 0 ? 0 : (v > kTok ? kTok : v));
     }
     for (int attempt = 0;; ++attempt) {
 #pragma unroll
-      for (int r = 0; r < kTiles; ++r) {
+      for (int r = 0; r < kNt; ++r) {
 #pragma unroll
         for (int i = 0; i < D / 16; ++i) st[r].o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         st[r].m = m_exact[r];
         st[r].l = 0.f;
         st[r].seen = kNegInf;
       }
-      if (attempt > 0 && wave < ((nstatic + 1) >> 1))
-        issue_pair<D, KV>(fa, win, nstatic, wave, kbase, vbase, blk_stride, ln, lq);
+      if (attempt > 0 && pairs0 != 0)
+        issue_pair<D, KV>(fa, win, nstatic, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
       // Windows of blocks: the unit's own entries first (one or two
       // windows), then (usually none) blocks its beams gained after the
       // metadata was built, read from the live block table 64 at a time. One
@@ -1157,13 +1394,14 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
       // piece.
       Window cw = win;
       int cn = nstatic;
+      uint64_t cpairs = pairs0;
       bool second = nstatic2 > 0;
       uint64_t ext_left = paged ? 0ull
                                 : __builtin_amdgcn_ballot_w64(lane >= nstatic && lane < nent &&
                                                               (u.ent_inf & kEntExt) != 0);
       int xb = 0, xnext = 0, xend = 0, xlen = 0, xa = 0, xe = 0;
       for (;;) {
-        run_window<D, KV>(cw, cn, nt, kbase, vbase, blk_stride, sc, qbuf, st, fa, wave, ln, lq);
+        run_window<D, KV>(cw, cn, nrows, ws, kbase, vbase, blk_stride, sc, qbuf, st, fa, cpairs, ln, lq);
         if (attempt == 0) TTS_PROF_MARK(1, rec_idx);
         // The next window: the unit's second one, else the next extension
         // window; one issue site below for both.
@@ -1183,8 +1421,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
             xlen = rl(ext_len, e);
             const int B = rl(ext_build, e);
             xb = __shfl(u.beam_l, rl(u.ent_id, e) & 15);
-            xa = rl(win.a, e);
-            xe = rl(win.e, e);
+            xa = win_a(rl(win.w, e));
+            xe = win_e(rl(win.w, e));
             xnext = (B + kTok - 1) / kTok;
             xend = (xlen + kTok - 1) / kTok;
             if (xlen < B) {
@@ -1214,10 +1452,11 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
           we = xe;
           xnext += cn;
         }
+        wave_has = true;
+#pragma unroll
+        for (int gq = 0; gq < kGroups; ++gq) nsrc[gq] = group_waves(ws, gq);
         cw.id = id;
-        cw.valid = v;
-        cw.a = wa;
-        cw.e = we;
+        cw.w = win_word(wa, we, v);
         cw.ks = 1.f;
         cw.vs = 1.f;
         if constexpr (KV == kKvFp8) {
@@ -1226,12 +1465,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
             cw.vs = p.v_scale[id];
           }
         }
-        if (wave < ((cn + 1) >> 1)) issue_pair<D, KV>(fa, cw, cn, wave, kbase, vbase, blk_stride, ln, lq);
+        cpairs = drop_pairs(group_pairs<KV>(cw, cn, ws.grp, lane), ws.sub);
+        if (cpairs != 0) issue_pair<D, KV>(fa, cw, cn, first_pair(cpairs), kbase, vbase, blk_stride, ln, lq);
       }
       if (attempt > 0) break;
       bool redo = false;
 #pragma unroll
-      for (int r = 0; r < kTiles; ++r) {
+      for (int r = 0; r < kNt; ++r) {
         const float mx = xlane_max16(st[r].seen);
         redo |= mx > kRefWindow || (mx < -kRefWindow && mx != kNegInf);
         m_exact[r] = mx == kNegInf ? 0.f : mx;
@@ -1247,84 +1487,101 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     if (nu_rows > 0) handover(nu);
 
     TTS_PROF_MARK(5, rec_idx);
-    // ---- combine the four waves' states, tile r by wave r ------------------
-    // (Every tile's row sums first, in straight-line code, so that their
-    // cross-lane reductions overlap.)
-    float lt_[kTiles];
+    // ---- combine the states of each group's waves --------------------------
+    // The waves publish their states in LDS, then sixteen threads per row
+    // sum them, in wave order. A wave that was given no pair publishes
+    // nothing and is not read.
 #pragma unroll
-    for (int r = 0; r < kTiles; ++r) lt_[r] = xlane_sum16(st[r].l);
+    for (int i = 0; i < kNt; ++i) st[i].l = xlane_sum16(st[i].l);
+    // A wave that saw no token of a row (l = 0: every score masked) keeps
+    // its initial reference; it must not set the maximum, or a row whose
+    // scores all lie far below it would lose every weight to underflow.
 #pragma unroll
-    for (int r = 0; r < kTiles; ++r) {
-      if (r < nt && r != wave) {
-        float* c = comb_slot(wave, r);
+    for (int i = 0; i < kNt; ++i)
+      if (!(st[i].l > 0.f)) st[i].m = kNegInf;
+#pragma unroll
+    for (int i = 0; i < kNt; ++i) {
+      if (wave_has && 16 * (ws.grp * kNt + i) < nrows) {
+        float* c = comb_slot(wave, i);
 #pragma unroll
         for (int dt = 0; dt < D / 16; ++dt)
-          *reinterpret_cast<f32x4*>(c + ln * G::comb_row + 16 * dt + 4 * lq) = st[r].o[dt];
+          *reinterpret_cast<f32x4*>(c + ln * G::comb_row + 16 * dt + 4 * lq) = st[i].o[dt];
         if (lq == 0) {
-          c[kTok * G::comb_row + ln] = st[r].m;
-          c[kTok * G::comb_row + kTok + ln] = lt_[r];
+          c[kTok * G::comb_row + ln] = st[i].m;
+          c[kTok * G::comb_row + kTok + ln] = st[i].l;
         }
       }
     }
     __syncthreads();
     TTS_PROF_MARK(6, rec_idx);
-    // Wave r combines tile r: its own state straight from registers (one
-    // code path per tile index, so nothing is copied), the other waves'
-    // from LDS, in wave order.
+    // Thread (tile, row, c), sixteen to a row, even tiles by the first four
+    // waves and odd ones by the others: stored elements (D / 16) c .. of the
+    // row, which are dimensions 16 t + 4 q + j (partial states' lane order).
+    {
 #pragma unroll
-    for (int r = 0; r < kTiles; ++r) {
-      if (r != wave || r >= nt) continue;
-      const int row = 16 * r + ln;
-      const float own_l = lt_[r];
-      // A wave that saw no token of the row (l = 0: no pair of it, or every
-      // score masked) keeps its initial reference; it must not set the
-      // maximum, or a row whose scores all lie far below it would lose every
-      // weight to underflow.
-      float mw[kWaves], lw[kWaves], mx = kNegInf;
+      for (int r = 0; r < kTiles; ++r) {
+        if ((r & 1) != (wave >> 2) || 16 * r >= nrows) continue;  // wave-uniform
+        constexpr int kEl = D / 16;
+        const int c16 = ln, rrow = (tid >> 4) & 15, row = 16 * r + rrow;
+        const int q4 = c16 >> 2, tt = (c16 & 3) * (kEl / 4);
+        const int w0 = group_first(ws, r / kNt), ns = nsrc[r / kNt], ti = r % kNt;
+        // (Past the last state the reads repeat the first place; what they
+        // bring is not used.)
+        float mw[kWaves], lw[kWaves], mx = kNegInf;
+        f32x4 ov[kWaves / 2][kEl / 4];
+        auto read_states = [&](int k0) {
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        lw[w] = (w == r) ? own_l : comb_slot(w, r)[kTok * G::comb_row + kTok + ln];
-        const float m = (w == r) ? st[r].m : comb_slot(w, r)[kTok * G::comb_row + ln];
-        mw[w] = lw[w] > 0.f ? m : kNegInf;
-        mx = fmaxf(mx, mw[w]);
-      }
-      float l = 0.f;
-      f32x4 o[D / 16];
+          for (int k = 0; k < kWaves / 2; ++k) {
+            const float* c = comb_slot(w0 + (k0 + k < ns ? k0 + k : 0), ti);
 #pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < kEl / 4; ++e)
+              ov[k][e] = *reinterpret_cast<const f32x4*>(c + rrow * G::comb_row + 16 * (tt + e) + 4 * q4);
+          }
+        };
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const float f = mw[w] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mw[w] - mx);
-        if (w == r) {
-          l += own_l * f;
-#pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) o[dt] += st[r].o[dt] * f;
-        } else {
-          const float* c = comb_slot(w, r);
-          l += lw[w] * f;
-          // All of the wave's reads first: read and add one at a time, the
-          // compiler waits for each read before issuing the next.
-          f32x4 t[D / 16];
-#pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt)
-            t[dt] = *reinterpret_cast<const f32x4*>(c + ln * G::comb_row + 16 * dt + 4 * lq);
-#pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) o[dt] += t[dt] * f;
+        for (int k = 0; k < kWaves; ++k) {
+          const float* c = comb_slot(w0 + (k < ns ? k : 0), ti) + kTok * G::comb_row + rrow;
+          mw[k] = c[0];
+          lw[k] = c[kTok];
         }
-      }
-      float m_fin = mx;
-      if ((bad_rows >> row) & 1ull) m_fin = __builtin_nanf("");
-      if (row < nrows) {
+        read_states(0);
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+          if (k >= ns) {
+            mw[k] = kNegInf;
+            lw[k] = 0.f;
+          }
+          mx = fmaxf(mx, mw[k]);
+        }
+        float l = 0.f;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+          mw[k] = mw[k] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mw[k] - mx);  // now the weight
+          l += lw[k] * mw[k];
+        }
+        f32x4 o[kEl / 4];
+#pragma unroll
+        for (int e = 0; e < kEl / 4; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+          if (k >= ns) break;  // uniform (no state at all: the row's beam holds no block here)
+          if (k == kWaves / 2) read_states(kWaves / 2);
+#pragma unroll
+          for (int e = 0; e < kEl / 4; ++e) o[e] += ov[k % (kWaves / 2)][e] * mw[k];
+        }
+        const bool bad = ((bad_rows >> row) & 1ull) != 0;
+        const float inv = l > 0.f ? 1.f / l : 0.f;
         if (paged && p.paged_nsplit == 1) {
           // Whole sequence in this unit: the normalised result.
-          float* orow = p.out + (static_cast<int64_t>(paged_b) * p.hq + kvh * p.g + row) * D;
-          const float inv = (l > 0.f) ? 1.f / l : 0.f;
-          const bool nan = m_fin != m_fin;
+          if (row < nrows) {
+            float* orow = p.out + (static_cast<int64_t>(paged_b) * p.hq + kvh * p.g + row) * D;
+            const float qnan = __builtin_nanf("");
 #pragma unroll
-          for (int dt = 0; dt < D / 16; ++dt) {
-            f32x4 v = o[dt] * inv;
-            if (nan) v = f32x4{m_fin, m_fin, m_fin, m_fin};
-            *reinterpret_cast<f32x4*>(orow + 16 * dt + 4 * lq) = v;
+            for (int e = 0; e < kEl / 4; ++e) {
+              f32x4 v = o[e] * inv;
+              if (bad) v = f32x4{qnan, qnan, qnan, qnan};
+              *reinterpret_cast<f32x4*>(orow + 16 * (tt + e) + 4 * q4) = v;
+            }
           }
         } else {
           int64_t prow;
@@ -1332,7 +1589,8 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
             prow = (static_cast<int64_t>(paged_b) * p.paged_nsplit + paged_split) * p.hq + kvh * p.g + row;
           else
             prow = static_cast<int64_t>(kvh) * p.rows_per_head + prow0 + row;
-          write_partial<D, KV>(p.part_o, p.part_ml, prow, o, m_fin, l, lq, true);
+          store_partial_row<D, KV>(p.part_o, p.part_ml, prow, o, bad ? __builtin_nanf("") : mx, l, inv, c16,
+                                   row < nrows);
         }
       }
     }
@@ -1345,7 +1603,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     if (nu_rows <= 0) break;
     rec_idx = unext;
     u = nu;
-    fa_ready = true;
   }
 }
 

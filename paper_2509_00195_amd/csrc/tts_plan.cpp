@@ -6,23 +6,23 @@
 // of KV blocks, each applying to a contiguous range of those rows. Two kinds
 // of unit cover every (beam, used block) exactly once per KV head:
 //
-// * Wide units. A segment shared by more beams than fit in a narrow unit
-//   (its rows exceed kMaxRows) is cut into row chunks of whole beams (up to
-//   kMaxWideRows rows, or kAltWideRows where the cost model finds that plan
-//   cheaper: the four waves of the workgroup share every block through
-//   LDS, each taking a quarter of the row tiles) and, along its
-//   blocks, into pieces; every (piece, chunk) is a unit whose blocks apply
-//   to all of its rows. (fp32 caches use chunks of kMaxRows rows.) The
-//   chunks of one piece read the same blocks and are placed on one XCD.
+// * Wide units. A segment of more rows than one wave group of a narrow unit
+//   takes (kGroupRows) is cut into row chunks of whole beams (up to
+//   kMaxWideRows rows, or a smaller cap the cost model picks; the eight waves
+//   of the workgroup share every block through LDS, each computing one or
+//   two row tiles) and, along its blocks, into pieces; every (piece, chunk)
+//   is a unit whose blocks apply to all of its rows. (Short pieces may go to
+//   narrow-mode units instead, and fp32 caches use only those.) The chunks
+//   of one piece read the same blocks and are placed on one XCD.
 // * Narrow units. Everything else -- segments of few beams and every beam's
 //   private tail -- is listed depth-first over the prefix tree (a segment's
 //   blocks, then its subtrees and the tails of the beams ending at it, in
 //   canonical order). Consecutive entries of that list always cover a
 //   contiguous range of beams, so the list is cut into units of at most
-//   kMaxUnitBeams beams / kMaxRows rows (kAltRows where the cost model
-//   finds that plan cheaper) / kMaxEntries entries and about equal cost: a
-//   small subtree with its tails becomes one unit and one partial state per
-//   beam instead of one per segment.
+//   kMaxUnitBeams beams / kMaxRows rows (kGroupRows in streaming batches) /
+//   kMaxUnitEntries entries and about equal cost: a small subtree with its
+//   tails becomes one unit and one partial state per beam instead of one per
+//   segment.
 //
 // Units are replicated per KV head, grouped, spread over the XCDs longest
 // first and then over each XCD's workgroups longest first.
@@ -36,67 +36,66 @@ namespace tts {
 namespace {
 
 // Cost model (microseconds of one workgroup, all compute units busy),
-// fitted to per-unit clock marks of the kernel at the 7B-shaped 64-beam
-// tree (D 128, bf16 KV, g 7): every unit pays a fixed part (its first
-// memory round trips, the end of its loop, the partial writes); a narrow
-// unit then streams its blocks at about 0.21 us per 8 KiB block and pays
-// about 0.08 us per query row (query read, combine, partial state); a wide
-// unit pays about 0.193 us per 8 KiB block for staging it through LDS plus
-// 0.113 us per block for each row tile a wave runs. (The narrow terms are
-// the least-squares fit scaled by 1.25: a plain fit under-predicts the
-// largest narrow units, which then finish last; the scale was chosen by
-// timing the kernel.) fp32 caches scale the block terms by their bytes and
-// every shape the tile term by the head size.
-constexpr double kUnitFixedUs = 4.9;
-constexpr double kNarrowUsPerByte = 0.2075 / 8192;
-constexpr double kRowUs = 0.08;  // per row of 256 + 272 bytes (query + partial state)
-constexpr double kWideUsPerByte = 0.193 / 8192;
-constexpr double kTileBlockUs = 0.113;  // per block and row tile of a wave, D = 128
-// fp8 caches: a block costs about what a bf16 block does (the products and
-// the conversion, not the bytes, set its time), so they take their own
-// terms, the least-squares fit to per-unit clock marks at the long-chain
-// batch (16 x 32 beams, fp8 KV, 1,772 units): narrow 3.30 us + 0.204 us
-// per block + 0.142 us per row, wide 4.60 us + 0.281 us per block + 0.093
-// us per block and row tile of a wave.
-constexpr double kFp8NarrowFixedUs = 3.30, kFp8NarrowBlockUs = 0.204, kFp8RowUs = 0.142;
-constexpr double kFp8WideFixedUs = 4.60, kFp8WideBlockUs = 0.281, kFp8TileBlockUs = 0.093;
-// When the units outnumber the workgroups (chained plans, where nearly every
-// compute unit streams private blocks from HBM the whole time) a narrow
-// unit's blocks take longer than at the 7B 64-beam tree: at the straggler
-// batch the clock marks put narrow units at 1.24x the model and wide ones at
-// 1.07x. Chained plans scale the bf16 narrow block term by 1.3 (1.15 to 1.6
-// were timed; 1.3 was the fastest).
-constexpr double kChainedNarrowScale = 1.3;
+// fitted to per-unit clock marks of the kernel at the 7B-shaped batches
+// (D 128, g 7; bf16: the 64-beam trees, the straggler batch and the
+// verification of four tokens; fp8: the long-chain batch). Every unit pays
+// a fixed part (its first memory round trips, the end of its loop, the
+// partial writes).
+// * Narrow: 3.0 us + 0.26 us per 8 KiB block (fp8: 0.225 us per 4 KiB one) +
+//   0.05 us per query row; with more than 32 rows, whose waves work in two
+//   groups, 1.5 us more, and blocks with rows of both groups count twice.
+// * Wide, up to eight row tiles (each half of the waves takes every other
+//   pair): 5.3 us + (0.27 + 0.011 tiles) us per 8 KiB block; more tiles:
+//   5.3 us + (0.12 + 0.029 tiles) us. fp8: 5.3 us + (0.175 + 0.0325 tiles)
+//   us per block, in both forms.
+// fp32 caches scale the block terms by their bytes and every shape the tile
+// term by the head size.
+constexpr double kNarrowFixedUs = 3.0, kNarrowBlockUs = 0.26, kRowUs = 0.05, kGroupsUs = 1.5;
+constexpr double kWideFixedUs = 5.3;
+constexpr double kHalvesBlockUs = 0.27, kHalvesTileUs = 0.011;
+constexpr double kFullBlockUs = 0.12, kFullTileUs = 0.029;
+constexpr double kFp8NarrowBlockUs = 0.225;
+constexpr double kFp8WideBlockUs = 0.175, kFp8WideTileUs = 0.0325;
+// Where the batch holds many bytes per workgroup the narrow units' blocks
+// come at the rate of the memory, not of one workgroup's round trips: 0.33
+// us per block with every workgroup streaming (straggler batch) against 0.26
+// where half of them run wide units (64-beam tree). Above this many KV bytes
+// per workgroup the bf16 narrow block term is scaled by 1.3.
+constexpr double kStreamBytesPerGroup = 400e3, kStreamScale = 1.3;
 constexpr int kXcds = 8;  // workgroup k of a launch runs on XCD k % 8
-constexpr int kAltWideRows = 128;  // the other wide-unit row cap the planner tries
-constexpr int kAltRows = 42;       // the other narrow-unit row cap (plans that fit the workgroups)
-// The merge (a second launch): a fixed cost plus one round trip to memory
-// per kMergeBatch partial states of the beam with the most.
+constexpr int kFewWideRows = 192, kStreamWideRows = 128;  // wide-unit row caps tried besides kMaxWideRows
+constexpr double kCapGain = 0.97;
+// The merge (a second launch): a fixed cost, and for the beam with the most
+// partial states their writing and reading.
 constexpr double kMergeFixedUs = 3.2;
-constexpr double kMergeBatchUs = 1.4;
+constexpr double kMergeSlotUs = 0.06;
+
+constexpr int kGroupRows = 32;  // rows of a narrow unit whose waves work in one group
 
 int tiles_of(int rows) { return (rows + 15) / 16; }
 
 struct CostModel {
   double blk_bytes, q_row_bytes, part_row_bytes, d_scale;
   bool fp8 = false;
-  double narrow_scale = 1.0;  // kChainedNarrowScale in chained plans
-  double row_us() const { return kRowUs * (q_row_bytes + part_row_bytes) / 528.0; }
-  double narrow_fixed() const { return fp8 ? kFp8NarrowFixedUs : kUnitFixedUs; }
-  double wide_fixed() const { return fp8 ? kFp8WideFixedUs : kUnitFixedUs; }
+  double narrow_scale = 1.0;  // kStreamScale where the batch is bound by streaming
+  double row_us() const { return kRowUs * (q_row_bytes + part_row_bytes) / 800.0; }
   // Narrow units: the waves split the block pairs, every wave runs every tile.
-  double narrow_us(int blocks, int rows) const {
-    if (fp8) return kFp8NarrowFixedUs + blocks * kFp8NarrowBlockUs + rows * kFp8RowUs;
-    return kUnitFixedUs + narrow_scale * blocks * blk_bytes * kNarrowUsPerByte + rows * row_us();
+  // span: the blocks with rows of both wave groups, which both read.
+  double narrow_us(int blocks, int span, int rows) const {
+    return kNarrowFixedUs + (rows > kGroupRows ? kGroupsUs : 0.0) + (blocks + span) * narrow_block_us() +
+           rows * row_us();
   }
-  // Wide units: every wave runs every pair on its quarter of the tiles.
-  double wide_us(int blocks, int rows) const {
-    const int tpw = (tiles_of(rows) + 3) / 4;
-    if (fp8) return kFp8WideFixedUs + blocks * (kFp8WideBlockUs + tpw * kFp8TileBlockUs * d_scale);
-    return kUnitFixedUs + blocks * (blk_bytes * kWideUsPerByte + tpw * kTileBlockUs * d_scale);
+  double narrow_block_us() const {
+    return fp8 ? kFp8NarrowBlockUs : narrow_scale * blk_bytes * (kNarrowBlockUs / 8192);
   }
-  // Bytes a unit moves: its blocks, its query rows, its partial states.
-  double bytes(int blocks, int rows) const { return blocks * blk_bytes + rows * (q_row_bytes + part_row_bytes); }
+  // Wide units: one block, all tiles.
+  double wide_block_us(int rows) const {
+    const int nt = tiles_of(rows);
+    if (fp8) return kFp8WideBlockUs + nt * kFp8WideTileUs * d_scale;
+    if (nt <= kUnitWaves) return blk_bytes * (kHalvesBlockUs / 8192) + nt * kHalvesTileUs * d_scale;
+    return blk_bytes * (kFullBlockUs / 8192) + nt * kFullTileUs * d_scale;
+  }
+  double wide_us(int blocks, int rows) const { return kWideFixedUs + blocks * wide_block_us(rows); }
 };
 
 struct Tmpl {
@@ -166,6 +165,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   cm.d_scale = shape.head_dim / 128.0;
   cm.fp8 = shape.kv_bytes == 1;
 
+  const bool streaming = static_cast<double>(m.unique_blocks) * hkv * cm.blk_bytes > kStreamBytesPerGroup * nbins;
+  if (streaming) cm.narrow_scale = kStreamScale;
+
   // ---- tree structure ----------------------------------------------------
   std::vector<std::vector<int32_t>> children(nseg), leaves(nseg);
   std::vector<std::vector<std::pair<int32_t, int32_t>>> top(std::max<size_t>(1, m.req_off.size()) - 1);
@@ -205,9 +207,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     }
     items.push_back({0, pos, pos + 1, 1, kEntExt});
   };
-  // Iterative walk: a stack of (segment, or -1 - leaf position). Which
-  // segments are wide (more beams than a narrow unit takes) depends on RB,
-  // so the list is made again for each narrow row cap.
+  // Iterative walk: a stack of (segment, or -1 - leaf position).
   std::vector<int32_t> stack;
   auto push_sorted = [&](std::vector<std::pair<int32_t, int32_t>>& v) {
     std::sort(v.begin(), v.end());
@@ -215,7 +215,12 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   };
   std::vector<std::pair<int32_t, int32_t>> tmp;
   auto list_items = [&]() {
-    for (int32_t s = 0; s < nseg; ++s) wide[s] = (m.seg_beam_end[s] - m.seg_beam_begin[s]) > RB;
+    // A segment of more rows than one wave group takes is cut into units of
+    // its own (left to narrow units of two groups, its blocks are read twice:
+    // 7B 64-beam tree 24.4 us per call against 23.1; fp32 caches: of more
+    // than a narrow unit takes).
+    const int32_t most = wide_mode ? narrow_beams(kGroupRows) : RB;
+    for (int32_t s = 0; s < nseg; ++s) wide[s] = (m.seg_beam_end[s] - m.seg_beam_begin[s]) > most;
     items.clear();
     for (auto& t : top) {
       push_sorted(t);
@@ -242,9 +247,11 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // ---- units for a target unit time T ------------------------------------
   // A wide segment of G beams and n blocks is cut into C row chunks and P
   // pieces, in the wide mode (chunks of up to RW beams) or the narrow mode
-  // (up to RB beams): the choice that moves the fewest bytes among those
-  // whose units fit T (else the fastest). The narrow list is cut greedily
-  // into units that fit T.
+  // (up to RB beams): among the choices whose units fit T the one with the
+  // least share of the modelled time, its units' time over the workgroups
+  // plus the merge of its pieces' states (else the fastest). The narrow list
+  // is cut greedily into units that fit T.
+  auto span_of = [&](int32_t blocks, int32_t rows) { return rows > kGroupRows ? blocks : 0; };
   auto make_templates = [&](double T, std::vector<Tmpl>& tm, int32_t& ngroups) {
     tm.clear();
     ngroups = 0;
@@ -254,7 +261,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       const int32_t n = m.seg_nblocks[s], np = (n + 1) / 2;
       struct Choice {
         int32_t mode, C, P;
-        double bytes, us;
+        double share, us;
       } best{kModeNarrow, 0, 0, 0, 0};
       bool have = false, best_fits = false;
       for (int32_t mode : {kModeWide, kModeNarrow}) {
@@ -265,17 +272,17 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
           const int32_t max_ent = mode == kModeWide ? kMaxUnitEntries : kMaxEntries;
           for (int32_t P = std::max(1, (n + max_ent - 1) / max_ent); P <= np; ++P) {
             const int32_t blocks = std::min(n, 2 * ((np + P - 1) / P));
-            const double us = mode == kModeWide ? cm.wide_us(blocks, rows) : cm.narrow_us(blocks, rows);
-            const double bytes = static_cast<double>(C) * P * cm.bytes(blocks, rows);
+            const double us = mode == kModeWide ? cm.wide_us(blocks, rows) : cm.narrow_us(blocks, span_of(blocks, rows), rows);
+            const double share = C * P * us * hkv / nbins + kMergeSlotUs * P;
             const bool fits = us <= T;
             const bool better = !have || (fits && !best_fits) ||
-                                (fits == best_fits && (fits ? bytes < best.bytes : us < best.us));
+                                (fits == best_fits && (fits ? share < best.share : us < best.us));
             if (better) {
-              best = {mode, C, P, bytes, us};
+              best = {mode, C, P, share, us};
               best_fits = fits;
               have = true;
             }
-            if (fits) break;  // more pieces only add bytes
+            if (fits) break;  // more pieces only add fixed parts
           }
         }
       }
@@ -294,7 +301,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
             t.info.push_back(t.mode == kModeWide ? 0u : ent_info(0, rows, bs, 0u));
           }
           t.nstatic = e - a;
-          t.cost = t.mode == kModeWide ? cm.wide_us(e - a, rows) : cm.narrow_us(e - a, rows);
+          t.cost = t.mode == kModeWide ? cm.wide_us(e - a, rows) : cm.narrow_us(e - a, span_of(e - a, rows), rows);
           t.group = ngroups;
           tm.push_back(std::move(t));
         }
@@ -303,7 +310,10 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     }
     Tmpl cur;
     std::vector<NItem> pend, ext;  // the open unit's static and extension items
-    int32_t nblk = 0;
+    int32_t nblk = 0, nspan = 0;
+    auto spans = [&](const NItem& it, int32_t lo) {
+      return (it.flags & kEntExt) == 0 && (it.p0 - lo) * g < kGroupRows && (it.p1 - lo) * g > kGroupRows;
+    };
     // A unit's entries: the first window holds its LIVE entries, static
     // entries up to 64 with the extension entries, which come last; the
     // second window the remaining static entries (the order of a unit's
@@ -334,12 +344,13 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       }
       for (const NItem* it : second) push(*it);
       cur.nstatic2 = static_cast<int32_t>(second.size());
-      cur.cost = cm.narrow_us(cur.nstatic + cur.nstatic2, (cur.hi - cur.lo) * g);
+      cur.cost = cm.narrow_us(cur.nstatic + cur.nstatic2, nspan, (cur.hi - cur.lo) * g);
       tm.push_back(std::move(cur));
       cur = Tmpl();
       pend.clear();
       ext.clear();
       nblk = 0;
+      nspan = 0;
     };
     for (const NItem& it : items) {
       const bool is_ext = (it.flags & kEntExt) != 0;
@@ -350,7 +361,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
         const int32_t live_ext = nlive + static_cast<int32_t>(ext.size()) +
                                  ((it.flags & (kEntLive | kEntExt)) ? 1 : 0);
         const bool fits = hi - lo <= RB && static_cast<int32_t>(pend.size() + ext.size()) + 1 <= kMaxUnitEntries &&
-                          live_ext <= kMaxEntries && cm.narrow_us(nblk + (is_ext ? 0 : 1), (hi - lo) * g) <= T;
+                          live_ext <= kMaxEntries && cm.narrow_us(nblk + (is_ext ? 0 : 1), nspan + (spans(it, lo) ? 1 : 0), (hi - lo) * g) <= T;
         if (!fits) flush();
       }
       if (pend.empty() && ext.empty()) {
@@ -364,6 +375,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       } else {
         pend.push_back(it);
         ++nblk;
+        nspan += spans(it, cur.lo) ? 1 : 0;
       }
     }
     flush();
@@ -440,33 +452,48 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   };
 
   // ---- target search ---------------------------------------------------------
-  // Every unit pays a fixed cost and the kernel is bound by memory
-  // bandwidth shared by all workgroups, so the best plan has one unit per
-  // workgroup, all of about equal cost: the smallest target T whose units
-  // (times the KV heads) still fit in the workgroups (a binary search; the
-  // unit count only falls as T grows). When even the largest units
-  // outnumber the workgroups, units are chained, and the target with the
-  // smallest predicted makespan over a grid of candidates is taken.
+  // Units of about equal cost: the smallest target T whose units (times the
+  // KV heads) fit in the workgroups, one each, is found by bisection (the
+  // unit count only falls as T grows). From there a few smaller targets,
+  // whose units are chained several to a workgroup, and larger ones, whose
+  // longer units leave fewer partial states to merge, are placed too, and
+  // the one with the least modelled time (the largest workgroup load plus
+  // the merge) is taken. When even the largest units outnumber the
+  // workgroups, the targets are taken around the average work.
   std::vector<Tmpl> tm;
   std::vector<std::vector<Work>> bins;
   int32_t ngroups = 0;
-  const int32_t fit_units = std::max(1, nbins / hkv);
+  // Units (of one KV head) that fit the workgroups one each. A batch with
+  // enough beams to fill half of them at four units per beam and head gets
+  // no more than that: few partial states per beam.
+  int32_t fit_units = std::max(1, nbins / hkv);
+  if (4 * S >= fit_units / 2) fit_units = std::min(fit_units, 4 * S);
+  const double target0 = kNarrowFixedUs;  // a unit's fixed part: targets scale what is above it
   auto units_at = [&](double T) {
     make_templates(T, tm, ngroups);
     return static_cast<int32_t>(tm.size());
   };
+  std::vector<char> touched;
+  std::vector<int32_t> slot_cnt;
+  auto merge_us = [&](const std::vector<Tmpl>& t) {
+    slot_cnt.assign(S, 0);
+    for (const Tmpl& x : t) {
+      touched_beams(x, g, &touched);
+      for (int32_t i = 0; i < x.hi - x.lo; ++i)
+        if (touched[i]) ++slot_cnt[m.perm[x.lo + i]];
+    }
+    const int32_t slots = S > 0 ? *std::max_element(slot_cnt.begin(), slot_cnt.end()) : 0;
+    return kMergeFixedUs + kMergeSlotUs * slots;
+  };
   // One search at the current RW: fills tm, bins, ngroups and the plan's
-  // target, work and chaining; returns the modelled time it minimised (the
-  // longest unit plus the merge for plans that fit the workgroups, the
-  // largest workgroup load for chained ones).
+  // target, work and chaining; returns the modelled time.
   auto search = [&]() {
-    cm.narrow_scale = 1.0;
-    double est = 0;
+    double est = -1;
     double work = 0;
     for (const NItem& it : items)
-      if (!(it.flags & kEntExt)) work += cm.narrow_us(1, 0) - cm.narrow_fixed();
+      if (!(it.flags & kEntExt)) work += cm.narrow_block_us();
     for (int32_t s = 0; s < nseg; ++s)
-      if (wide[s]) work += cm.wide_us(m.seg_nblocks[s], RW * g) - cm.wide_fixed();
+      if (wide[s]) work += m.seg_nblocks[s] * cm.wide_block_us(RW * g);
     work = work * hkv / nbins;
     P.work_us = work;
     P.chained = false;
@@ -474,130 +501,94 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       // Warm re-plan: the earlier target, scaled with the work, raised while
       // its units outnumber the workgroups (unless that plan was chained);
       // one placement, no search.
-      double T = kUnitFixedUs + (warm->target_us - kUnitFixedUs) * (work / warm->work_us);
-      T = std::max(T, kUnitFixedUs + 1e-3);
+      double T = target0 + (warm->target_us - target0) * (work / warm->work_us);
+      T = std::max(T, target0 + 1e-3);
       if (!warm->chained)
-        for (int it = 0; it < 12 && units_at(T) > fit_units; ++it) T = kUnitFixedUs + 1.15 * (T - kUnitFixedUs);
+        for (int it = 0; it < 12 && units_at(T) > fit_units; ++it) T = target0 + 1.15 * (T - target0);
       units_at(T);
       est = place(tm, ngroups, bins);
       P.target_us = T;
       P.chained = warm->chained;
-    } else {
-      // Upper bound of the search: a few times the average work per unit,
-      // raised while the units do not fit (one entry of many rows can cost
-      // more than that bound by its row term alone; without the raise such a
-      // batch would fall to the chained plans, with one tiny unit per entry).
-      double hi = kUnitFixedUs + 4.0 * work + 1.0;
-      for (int it = 0; it < 6 && units_at(hi) > fit_units; ++it) hi *= 2.0;
-      if (units_at(hi) <= fit_units) {
-        double lo = kUnitFixedUs;
-        for (int it = 0; it < 24; ++it) {
-          const double mid = 0.5 * (lo + hi);
-          if (units_at(mid) <= fit_units)
-            hi = mid;
-          else
-            lo = mid;
-        }
-        // Longer units mean fewer partial states per beam, so a cheaper merge:
-        // take the target (the smallest one's variable part scaled up) with the
-        // least modelled attention plus merge time.
-        std::vector<char> touched;
-        auto most_slots = [&](const std::vector<Tmpl>& t) {
-          std::vector<int32_t> cnt(S, 0);
-          for (const Tmpl& x : t) {
-            touched_beams(x, g, &touched);
-            for (int32_t i = 0; i < x.hi - x.lo; ++i)
-              if (touched[i]) ++cnt[m.perm[x.lo + i]];
-          }
-          return S > 0 ? *std::max_element(cnt.begin(), cnt.end()) : 0;
-        };
-        const double t_min = hi;
-        double best_T = t_min, best_est = -1;
-        for (double f : {1.0, 1.5, 2.0, 3.0, 4.0, 6.0}) {
-          const double T = kUnitFixedUs + f * (t_min - kUnitFixedUs);
-          if (units_at(T) > fit_units) continue;
-          double ms = 0;
-          for (const Tmpl& x : tm) ms = std::max(ms, x.cost);
-          const int32_t slots = most_slots(tm);
-          const double est = ms + kMergeFixedUs + kMergeBatchUs * ((slots + kMergeBatch - 1) / kMergeBatch);
-          if (best_est < 0 || est < best_est) {
-            best_est = est;
-            best_T = T;
-          }
-        }
-        units_at(best_T);
-        place(tm, ngroups, bins);
-        P.target_us = best_T;
-        est = best_est;
-      } else {
-        std::vector<Tmpl> cand;
-        std::vector<std::vector<Work>> cbins;
-        double best = -1;
-        cm.narrow_scale = kChainedNarrowScale;
-        for (double f : {0.35, 0.5, 0.65, 0.8, 1.0, 1.2, 1.45, 1.75, 2.1, 2.5, 3.0, 4.0}) {
-          int32_t cg = 0;
-          make_templates(kUnitFixedUs + f * work, cand, cg);
-          const double ms = place(cand, cg, cbins);
-          if (best < 0 || ms < best) {
-            best = ms;
-            tm.swap(cand);
-            bins.swap(cbins);
-            ngroups = cg;
-            P.target_us = kUnitFixedUs + f * work;
-          }
-        }
-        P.chained = true;
-        est = best;
-      }
+      return est;
     }
+    // Upper bound of the bisection: a few times the average work per unit,
+    // raised while the units do not fit (one entry of many rows can cost
+    // more than that bound by its row term alone).
+    double base = work;
+    double hi = target0 + 4.0 * work + 4.0;
+    for (int it = 0; it < 6 && units_at(hi) > fit_units; ++it) hi *= 2.0;
+    const bool fits = static_cast<int32_t>(tm.size()) <= fit_units;
+    if (fits) {
+      double lo = target0;
+      for (int it = 0; it < 12; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (units_at(mid) <= fit_units)
+          hi = mid;
+        else
+          lo = mid;
+      }
+      base = hi - target0;
+    }
+    std::vector<Tmpl> cand;
+    std::vector<std::vector<Work>> cbins;
+    auto try_target = [&](double T) {
+      int32_t cg = 0;
+      make_templates(T, cand, cg);
+      if (static_cast<int32_t>(cand.size()) > fit_units && 4 * S < nbins / hkv && est >= 0) return;
+      const double e = place(cand, cg, cbins) + merge_us(cand);
+      if (est >= 0 && e >= est) return;
+      est = e;
+      P.chained = static_cast<int32_t>(cand.size()) * hkv > nbins;
+      tm.swap(cand);
+      bins.swap(cbins);
+      ngroups = cg;
+      P.target_us = T;
+    };
+    if (fits)
+      for (double f : {1.0, 0.5, 0.6, 0.75, 1.15, 1.3, 1.5, 1.75, 2.0, 2.5, 3.0, 4.0}) try_target(target0 + f * base);
+    else
+      for (double f : {0.35, 0.5, 0.65, 0.8, 1.0, 1.2, 1.45, 1.75, 2.1, 2.5, 3.0, 4.0}) try_target(target0 + f * base);
     return est;
   };
 
-  // Row caps. Wide units of up to kMaxWideRows rows (three row tiles per
-  // wave) or of up to kAltWideRows (two): fewer rows per chunk means more
-  // chunks that stage the same blocks, but shorter units to balance. Then,
-  // for plans that fit the workgroups, narrow units of up to kAltRows rows
-  // instead of kMaxRows: more, shorter units. The model picks, comparing
-  // plans of one kind only (both fit the workgroups, or both are chained);
-  // a candidate must model strictly faster. Measured: 7B 64-beam tree 192 /
-  // 64 rows; balanced tree and straggler batch 128-row wide units (-1.3 and
-  // -1.7 us per call); 1.5B 16-beam tree 42-row narrow units (-1.5 us). A
-  // warm re-plan keeps the earlier plan's caps.
-  if (warm && warm->target_us > 0 && warm->work_us > 0) {
-    P.wide_rows = warm->wide_rows > 0 ? warm->wide_rows : kMaxWideRows;
-    P.narrow_rows = warm->narrow_rows > 0 ? warm->narrow_rows : kMaxRows;
-    RB = narrow_beams(P.narrow_rows);
-    RW = wide_beams(P.wide_rows);
+  // Row caps of wide and of narrow units; the model picks, and a second
+  // choice has to model faster by the model's own error (kCapGain).
+  // * A streaming batch takes narrow units of up to 32 rows (one wave group;
+  //   straggler batch 86 us per call against 92 to 100 with 64 rows) and wide
+  //   units of up to 128, or of up to 256 where that models faster (long
+  //   chain 289 us per call with 256-row units, 302 with 192, 325 with 128).
+  // * Other batches take narrow units of up to 64 rows (7B 64-beam tree 23.1
+  //   us per call against 24.2 with 32) and wide units of up to 192 rows, or
+  //   256.
+  // A warm re-plan keeps the earlier plan's caps.
+  auto set_caps = [&](int32_t wide_rows, int32_t narrow_rows) {
+    P.wide_rows = wide_rows;
+    P.narrow_rows = narrow_rows;
+    RB = narrow_beams(narrow_rows);
+    RW = wide_beams(wide_rows);
     list_items();
+  };
+  if (warm && warm->target_us > 0 && warm->work_us > 0 && warm->wide_rows > 0) {
+    set_caps(warm->wide_rows, warm->narrow_rows);
     search();
   } else {
-    P.wide_rows = kMaxWideRows;
-    P.narrow_rows = kMaxRows;
-    RW = wide_beams(kMaxWideRows);
-    list_items();
+    set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming ? kGroupRows : kMaxRows);
     double best = search();
-    // Runs the search at caps (wide, narrow) and keeps it if it models
-    // faster than the plan at hand, else restores that plan.
-    auto try_caps = [&](int32_t wide_rows, int32_t narrow_rows) {
+    // Runs the search at another wide cap and keeps it if it models faster
+    // than the plan at hand, else restores that plan.
+    auto try_caps = [&](int32_t wide_rows) {
       std::vector<Tmpl> tm0 = tm;
       std::vector<std::vector<Work>> bins0 = bins;
-      const int32_t ngroups0 = ngroups, RW0 = RW, RB0 = RB;
+      const int32_t ngroups0 = ngroups, wide0 = P.wide_rows;
       const double target0 = P.target_us, work0 = P.work_us;
       const bool chained0 = P.chained;
-      RB = narrow_beams(narrow_rows);
-      RW = wide_beams(wide_rows);
-      if (RB != RB0) list_items();
+      set_caps(wide_rows, P.narrow_rows);
       const double alt = search();
-      if (P.chained == chained0 && alt < best) {
+      if (alt < kCapGain * best) {
         best = alt;
-        P.wide_rows = wide_rows;
-        P.narrow_rows = narrow_rows;
         return;
       }
-      RW = RW0;
-      const bool relist = RB != RB0;
-      RB = RB0;
-      if (relist) list_items();
+      set_caps(wide0, P.narrow_rows);
       tm.swap(tm0);
       bins.swap(bins0);
       ngroups = ngroups0;
@@ -605,8 +596,15 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       P.work_us = work0;
       P.chained = chained0;
     };
-    if (wide_mode && wide_beams(kAltWideRows) != RW) try_caps(kAltWideRows, P.narrow_rows);
-    if (!P.chained && narrow_beams(kAltRows) != RB) try_caps(P.wide_rows, kAltRows);
+    // (A cap under which every segment is cut into as many chunks as under
+    // the other gives the same plan.)
+    bool chunks_differ = false;
+    const int32_t most = wide_beams(kMaxWideRows);
+    for (int32_t s = 0; s < nseg && wide_mode; ++s) {
+      const int32_t G = m.seg_beam_end[s] - m.seg_beam_begin[s];
+      if (wide[s] && (G + RW - 1) / RW != (G + most - 1) / most) chunks_differ = true;
+    }
+    if (chunks_differ) try_caps(kMaxWideRows);
   }
 
   // ---- partial rows and merge lists ----------------------------------------
@@ -630,7 +628,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   P.num_slots = static_cast<int64_t>(P.slot_rows.size());
   size_t most = 0;
   for (const auto& v : per_beam) most = std::max(most, v.size());
-  P.slot_stride = std::max<int32_t>(kMergeBatch + 1, static_cast<int32_t>((most + 1 + 15) / 16 * 16));
+  P.slot_stride = static_cast<int32_t>((most + 1 + 15) / 16 * 16);
   P.slot_tab.assign(static_cast<size_t>(S) * P.slot_stride, 0);
   for (int32_t b = 0; b < S; ++b) {
     int32_t* row = P.slot_tab.data() + static_cast<size_t>(b) * P.slot_stride;
@@ -639,6 +637,21 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   }
 
   // ---- records ---------------------------------------------------------------
+  // Waves of the first of a narrow unit's two wave groups (UnitRec::mode;
+  // rows 0 .. 31 and the rest, for fp32 caches 0 .. 15): in proportion to
+  // the block entries with rows of each group.
+  auto first_group_waves = [&](const Tmpl& t) {
+    const int32_t cut = wide_mode ? kGroupRows : kGroupRows / 2;
+    int32_t c0 = 0, c1 = 0;
+    for (size_t k = 0; t.mode == kModeNarrow && k < t.ids.size(); ++k) {
+      if (t.info[k] & kEntExt) continue;
+      const int32_t r0 = t.info[k] & 63, r1 = ((t.info[k] >> 6) & 63) + 1;
+      c0 += r0 < cut;
+      c1 += r1 > cut;
+    }
+    const int32_t n = c0 + c1 > 0 ? (kUnitWaves * c0 + (c0 + c1) / 2) / (c0 + c1) : kUnitWaves / 2;
+    return std::min(kUnitWaves - 1, std::max(1, n));
+  };
   auto make_rec = [&](const Work& w) {
     UnitRec r{};
     const Tmpl& t = tm[w.t];
@@ -648,7 +661,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     r.nent = static_cast<int32_t>(t.ids.size());
     r.prow0 = prow0[w.t];
     r.next = -1;
-    r.mode = t.mode;
+    r.mode = t.mode | first_group_waves(t) << 8;
     for (int32_t i = 0; i < t.hi - t.lo; ++i) r.beams[i] = m.perm[t.lo + i];
     // First window: entries [0, n1); second window: the rest.
     const size_t n1 = t.ids.size() - static_cast<size_t>(t.mode == kModeWide ? std::max(0, t.nstatic - kMaxEntries)

@@ -38,10 +38,14 @@ inline constexpr uint32_t ent_info(int r0, int r1, int valid, uint32_t flags) {
 }
 
 // Wide units (kModeWide): up to kMaxWideRows rows of one segment piece;
-// each of the 4 waves owns a quarter of the row tiles (at most 3) and
+// each of the 8 waves owns an eighth of the row tiles (at most 2) and
 // every block applies to every row.
-constexpr int kMaxWideRows = 192;
+constexpr int kMaxWideRows = 256;
 constexpr int kMaxWideBeams = 64;
+// Waves of a workgroup. The waves of a narrow unit of more than 32 rows work
+// in two groups, rows 0 .. 31 and the rest (fp32 caches: of more than 16 rows
+// in two, of more than 32 in four, 16 rows each).
+constexpr int kUnitWaves = 8;
 enum UnitMode : int32_t { kModeNarrow = 0, kModeWide = 1 };
 
 // One unit of work: query rows of up to kMaxUnitBeams beams (kMaxWideBeams
@@ -57,7 +61,7 @@ struct UnitRec {
   int32_t nent;      // first window: block entries + extension entries (these come last)
   int32_t prow0;
   int32_t next;      // next record of the same workgroup, -1 at the end
-  int32_t mode;      // UnitMode
+  int32_t mode;      // UnitMode, and from bit 8 the waves of a narrow unit's first wave group
   int32_t nstatic2;  // second window: block entries (no LIVE or extension entries)
   int32_t beams[kMaxWideBeams];  // original beam index of each unit beam
   int32_t ent_id[kMaxEntries];   // physical block id (extension: beam slot)
@@ -113,9 +117,6 @@ struct AttnParams {
   int32_t two_windows;
 };
 
-// Slots per step of the planner's merge cost, and the smallest slot-table
-// stride - 1.
-constexpr int kMergeBatch = 16;
 // Readable int32 words after the start of any slot-table row (the table is
 // followed by this many zeros): the merge reads a row's first 64 entries in
 // the same round trip as its count, without waiting for the count.
