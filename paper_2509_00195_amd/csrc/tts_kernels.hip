@@ -944,7 +944,9 @@ __device__ __forceinline__ void store_q(const QRegs<D, KV>& qr, unsigned char* q
   }
 }
 
-template <int D, int KV, bool kWin2>
+// kWin2: some unit of the plan has a second entry window. kPaged: the paged
+// path, whose units come from the workgroup id and not from records.
+template <int D, int KV, bool kWin2, bool kPaged>
 __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   using G = Geo<D, KV>;
   using Q = QLds<D, KV>;
@@ -986,11 +988,14 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   };
   coords();
   const size_t blk_stride = static_cast<size_t>(p.hkv) * G::blk_bytes;
-  const bool paged = p.recs == nullptr;
+  constexpr bool paged = kPaged;
   const float sc_w = p.scale_log2;
   const float sc = p.scale_log2;
   auto comb_slot = [&](int w, int i) { return comb + (w * kNt + i) * G::comb_floats; };  // (wave, its tile)
 
+  // The parameters of the first steps in one read.
+  asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.recs), "s"(p.seq_lens), "s"(p.build_len),
+               "s"(p.hq), "s"(p.hkv), "s"(p.g), "s"(p.q_len));
   // ---- first unit -----------------------------------------------------------
   int rec_idx;
   UnitRegs u;
@@ -1017,9 +1022,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     u.ent_inf = 0;
     u.nstatic2 = 0;
   }
-  if (rfl(u.nrows) <= 0) return;
   QRegs<D, KV> qr;
-  load_q<D, KV>(p, u, qr, tid);
   Frags<D, KV> fa;
   bool fa_ready = false;  // the unit's first pair and lengths are in flight
   // fp32 at D = 128: a pair is 128 registers, too many to hold while the
@@ -1058,6 +1061,18 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     }
     fa_ready = true;
   };
+  // The record's loads all go out before any is waited for (left to itself
+  // the compiler moves most of them behind the wait for the header and the
+  // test of it), then the first unit's query rows, first pair and lengths
+  // together (in the unit's own code the pair waited for the query rows). An
+  // idle workgroup's record holds no rows and names beam 0, so its loads are
+  // in bounds.
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (kPaged)
+    load_q<D, KV>(p, u, qr, tid);
+  else
+    handover(u);
+  if (rfl(u.nrows) <= 0) return;
 
   for (;;) {
     coords();
@@ -1068,7 +1083,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     const unsigned char* kbase = static_cast<const unsigned char*>(p.k_cache) + kvh * G::blk_bytes;
     const unsigned char* vbase = static_cast<const unsigned char*>(p.v_cache) + kvh * G::blk_bytes;
 
-    if constexpr (KV != kKvF32) {
+    if constexpr (KV != kKvF32 && !kPaged) {
       if ((u.mode & 0xff) == kModeWide) {
         // ---- wide unit: every block pair is copied to an LDS stage once and
         // read from there. Up to eight row tiles: four waves hold all of them
@@ -1346,18 +1361,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
       win2_lds[lane] = uint2{static_cast<uint32_t>(id2), inf2};
     }
     const Split ws = split_waves<KV>(nrows, u.mode >> 8, wave);
-    const uint64_t pairs0 = drop_pairs(group_pairs<KV>(win, nstatic, ws.grp, lane), ws.sub);
-    // Waves of each group that are given a pair: those of its first window,
-    // or all (when the unit has more windows).
-    bool wave_has = pairs0 != 0;
-    int nsrc[kGroups];
-#pragma unroll
-    for (int gq = 0; gq < kGroups; ++gq) {
-      const int c = __builtin_popcountll(group_pairs<KV>(win, nstatic, gq, lane)), n = group_waves(ws, gq);
-      nsrc[gq] = c < n ? c : n;
-    }
-    if (!fa_ready && pairs0 != 0)
-      issue_pair<D, KV>(fa, win, nstatic, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
+    const uint64_t pairs_static = drop_pairs(group_pairs<KV>(win, nstatic, ws.grp, lane), ws.sub);
+    if (!fa_ready && pairs_static != 0)
+      issue_pair<D, KV>(fa, win, nstatic, first_pair(pairs_static), kbase, vbase, blk_stride, ln, lq);
     // The next unit's record: it has this unit's pair loop to arrive.
     nu.nrows = 0;
     if (unext >= 0) nu = load_unit(p.recs, unext, lane);
@@ -1376,6 +1382,101 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
       const int v = win_valid(win.w) + (ext_len - ext_build);
       win.w = win_word(win_a(win.w), win_e(win.w), v < 0 ? 0 : (v > kTok ? kTok : v));
     }
+    // ---- blocks its beams gained after the metadata was built ---------------
+    // Numbered over the unit's beams and packed into windows of 64, whatever
+    // beam they belong to, and in the first window where they fit: read beam
+    // by beam, every beam cost a round trip to the table and one to its
+    // blocks (append and call on the 7B 64-beam tree, 100 tokens on: 34.3 us
+    // against 32.0; what is left of growth is its bytes and the balance of a
+    // plan made without it).
+    int grow = 0, first_new = 0;  // lane e (extension entry): blocks gained, the first one
+    if (!paged && lane >= nstatic && lane < nent && (u.ent_inf & kEntExt) != 0) {
+      first_new = (ext_build + kTok - 1) / kTok;
+      // (Shorter than at build time: the merge reports NaN.)
+      if (ext_len >= ext_build) grow = (ext_len + kTok - 1) / kTok - first_new;
+    }
+    auto rows_mask = [](uint32_t w) {
+      const int a = win_a(w), e = win_e(w);
+      return (e >= 64 ? ~0ull : ((1ull << e) - 1)) & ~((1ull << a) - 1);
+    };
+    // A beam longer than its table row: NaN rows.
+    for (uint64_t over = __builtin_amdgcn_ballot_w64(grow > 0 && first_new + grow > p.max_blocks); over != 0;
+         over &= over - 1) {
+      bad_rows |= rows_mask(rl(win.w, static_cast<int>(__builtin_ctzll(over))));
+    }
+    if (first_new + grow > p.max_blocks) grow = 0;
+    const uint64_t grown = __builtin_amdgcn_ballot_w64(grow > 0);
+    int ngrown = 0;
+    for (uint64_t left = grown; left != 0; left &= left - 1) ngrown += rl(grow, static_cast<int>(__builtin_ctzll(left)));
+    // Entries t0, t0 + 1, ... of them into lanes l0 .. of id and w.
+    auto new_entries = [&](int t0, int l0, int* id, uint32_t* w) {
+      int beam = -1, j = 0, len = 0;
+      uint32_t inf = 0;
+      int at = l0 - t0;
+      for (uint64_t left = grown; left != 0; left &= left - 1) {
+        const int e = static_cast<int>(__builtin_ctzll(left));
+        const int n = rl(grow, e);
+        if (lane >= l0 && lane >= at && lane < at + n) {
+          beam = rl(u.beam_l, rl(u.ent_id, e) & 15);
+          j = rl(first_new, e) + lane - at;
+          len = rl(ext_len, e);
+          inf = rl(static_cast<int>(u.ent_inf), e);
+        }
+        at += n;
+      }
+      bool bad = false;
+      if (beam >= 0) {
+        if (p.q_len > 1) beam /= p.q_len;
+        int x = p.block_tables[static_cast<int64_t>(beam) * p.max_blocks + j];
+        int v = len - j * kTok;
+        v = v < kTok ? v : kTok;
+        bad = x < 0 || x >= p.num_blocks;
+        if (bad) {
+          x = 0;
+          v = 0;
+        }
+        *id = x;
+        *w = win_word(ent_r0(inf), ent_r1(inf), v);
+      }
+      for (uint64_t m = __builtin_amdgcn_ballot_w64(bad); m != 0; m &= m - 1)
+        bad_rows |= rows_mask(rl(*w, static_cast<int>(__builtin_ctzll(m))));
+    };
+    // In the first window they start at an even place, so that the pairs of
+    // its own entries stay as they are (an odd last one is paired with a
+    // repeat of itself that holds no token).
+    const int new0 = (nstatic + 1) & ~1;
+    int nfirst = nstatic, next_new = 0;
+    if (ngrown > 0 && new0 + ngrown <= kMaxEntries) {
+      if (nstatic & 1) {
+        const int last_id = rl(win.id, nstatic - 1);
+        const uint32_t last_w = rl(win.w, nstatic - 1);
+        if (lane == nstatic) {
+          win.id = last_id;
+          win.w = win_word(win_a(last_w), win_e(last_w), 0);
+        }
+      }
+      new_entries(0, new0, &win.id, &win.w);
+      if constexpr (KV == kKvFp8) {
+        if (lane >= new0 && lane < new0 + ngrown && win_valid(win.w) > 0) {
+          win.ks = p.k_scale[win.id];
+          win.vs = p.v_scale[win.id];
+        }
+      }
+      nfirst = new0 + ngrown;
+      next_new = ngrown;
+    }
+    const uint64_t pairs0 = drop_pairs(group_pairs<KV>(win, nfirst, ws.grp, lane), ws.sub);
+    if (pairs_static == 0 && pairs0 != 0)
+      issue_pair<D, KV>(fa, win, nfirst, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
+    // Waves of each group that are given a pair: those of its first window,
+    // or all (when the unit has more windows).
+    bool wave_has = pairs0 != 0;
+    int nsrc[kGroups];
+#pragma unroll
+    for (int gq = 0; gq < kGroups; ++gq) {
+      const int c = __builtin_popcountll(group_pairs<KV>(win, nfirst, gq, lane)), n = group_waves(ws, gq);
+      nsrc[gq] = c < n ? c : n;
+    }
     for (int attempt = 0;; ++attempt) {
 #pragma unroll
       for (int r = 0; r < kNt; ++r) {
@@ -1386,81 +1487,45 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         st[r].seen = kNegInf;
       }
       if (attempt > 0 && pairs0 != 0)
-        issue_pair<D, KV>(fa, win, nstatic, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
+        issue_pair<D, KV>(fa, win, nfirst, first_pair(pairs0), kbase, vbase, blk_stride, ln, lq);
       // Windows of blocks: the unit's own entries first (one or two
-      // windows), then (usually none) blocks its beams gained after the
-      // metadata was built, read from the live block table 64 at a time. One
+      // windows), then what its beams gained and the first had no room for,
+      // 64 at a time. One
       // call site keeps the register allocation of the pair loop in one
       // piece.
       Window cw = win;
-      int cn = nstatic;
+      int cn = nfirst;
       uint64_t cpairs = pairs0;
       bool second = nstatic2 > 0;
-      uint64_t ext_left = paged ? 0ull
-                                : __builtin_amdgcn_ballot_w64(lane >= nstatic && lane < nent &&
-                                                              (u.ent_inf & kEntExt) != 0);
-      int xb = 0, xnext = 0, xend = 0, xlen = 0, xa = 0, xe = 0;
+      int done_new = next_new;
       for (;;) {
         run_window<D, KV>(cw, cn, nrows, ws, kbase, vbase, blk_stride, sc, qbuf, st, fa, cpairs, ln, lq);
         if (attempt == 0) TTS_PROF_MARK(1, rec_idx);
-        // The next window: the unit's second one, else the next extension
-        // window; one issue site below for both.
-        int id = 0, v = 0, wa, we;
+        // The next window: the unit's second one, else the next of gained
+        // blocks; one issue site below for both.
+        int id = 0;
+        uint32_t w = win_word(0, 1, 0);
         if (second) {
           second = false;
           cn = nstatic2;
           const uint2 w2 = win2_lds[lane];
           id = static_cast<int>(w2.x);
-          v = lane < cn ? ent_valid(w2.y) : 0;
-          wa = ent_r0(w2.y);
-          we = ent_r1(w2.y);
+          w = win_word(ent_r0(w2.y), ent_r1(w2.y), lane < cn ? ent_valid(w2.y) : 0);
         } else {
-          while (xnext >= xend && ext_left != 0) {
-            const int e = static_cast<int>(__builtin_ctzll(ext_left));
-            ext_left &= ext_left - 1;
-            xlen = rl(ext_len, e);
-            const int B = rl(ext_build, e);
-            xb = __shfl(u.beam_l, rl(u.ent_id, e) & 15);
-            xa = win_a(rl(win.w, e));
-            xe = win_e(rl(win.w, e));
-            xnext = (B + kTok - 1) / kTok;
-            xend = (xlen + kTok - 1) / kTok;
-            if (xlen < B) {
-              xend = xnext;  // shorter than at build time: the merge reports NaN
-            } else if (xend > p.max_blocks) {
-              xend = xnext;  // longer than its table row: NaN rows
-              bad_rows |= (xe >= 64 ? ~0ull : ((1ull << xe) - 1)) & ~((1ull << xa) - 1);
-            }
-          }
-          if (xnext >= xend) break;
-          cn = (xend - xnext) < kMaxEntries ? (xend - xnext) : kMaxEntries;
-          bool xbad = false;
-          if (lane < cn) {
-            const int j = xnext + lane;
-            id = p.block_tables[static_cast<int64_t>(xb / p.q_len) * p.max_blocks + j];
-            v = xlen - j * kTok;
-            v = v < kTok ? v : kTok;
-            if (id < 0 || id >= p.num_blocks) {
-              xbad = true;
-              id = 0;
-              v = 0;
-            }
-          }
-          if (__builtin_amdgcn_ballot_w64(xbad) != 0)
-            bad_rows |= (xe >= 64 ? ~0ull : ((1ull << xe) - 1)) & ~((1ull << xa) - 1);
-          wa = xa;
-          we = xe;
-          xnext += cn;
+          if (done_new >= ngrown) break;
+          cn = (ngrown - done_new) < kMaxEntries ? (ngrown - done_new) : kMaxEntries;
+          new_entries(done_new, 0, &id, &w);
+          done_new += cn;
         }
         wave_has = true;
 #pragma unroll
         for (int gq = 0; gq < kGroups; ++gq) nsrc[gq] = group_waves(ws, gq);
         cw.id = id;
-        cw.w = win_word(wa, we, v);
+        cw.w = w;
         cw.ks = 1.f;
         cw.vs = 1.f;
         if constexpr (KV == kKvFp8) {
-          if (v > 0) {
+          if (win_valid(w) > 0) {
             cw.ks = p.k_scale[id];
             cw.vs = p.v_scale[id];
           }
@@ -1750,10 +1815,12 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
 
 template <int D, int KV>
 static hipError_t launch_attn_t(const AttnParams& p, int grid, hipStream_t stream) {
-  if (p.two_windows)
-    hipLaunchKernelGGL((attn_kernel<D, KV, true>), dim3(grid), dim3(kThreads), 0, stream, p);
+  if (p.recs == nullptr)
+    hipLaunchKernelGGL((attn_kernel<D, KV, false, true>), dim3(grid), dim3(kThreads), 0, stream, p);
+  else if (p.two_windows)
+    hipLaunchKernelGGL((attn_kernel<D, KV, true, false>), dim3(grid), dim3(kThreads), 0, stream, p);
   else
-    hipLaunchKernelGGL((attn_kernel<D, KV, false>), dim3(grid), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL((attn_kernel<D, KV, false, false>), dim3(grid), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 
