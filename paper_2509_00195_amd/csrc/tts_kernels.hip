@@ -1863,7 +1863,6 @@ hipError_t launch_attn(const AttnParams& p, int grid, int head_dim, int kv_kind,
 // process ends. In host code the name `scratch` is only a stand-in; the
 // device address comes from hipGetSymbolAddress, looked up once per device
 // with that device current.
-constexpr size_t kScratchBytes = size_t{64} << 20;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kScratchMaxDevices = 64;

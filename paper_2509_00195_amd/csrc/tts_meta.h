@@ -78,6 +78,7 @@ struct WorkPlan {
   bool chained = false;
   int32_t wide_rows = 0;    // the row caps of the wide and the narrow units
   int32_t narrow_rows = 0;  // the plan chose
+  bool few_states = false;  // units chosen so that the states fit the scratch array
 };
 
 struct PlanShape {

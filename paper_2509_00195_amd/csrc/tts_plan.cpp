@@ -218,8 +218,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     // A segment of more rows than one wave group takes is cut into units of
     // its own (left to narrow units of two groups, its blocks are read twice:
     // 7B 64-beam tree 24.4 us per call against 23.1; fp32 caches: of more
-    // than a narrow unit takes).
-    const int32_t most = wide_mode ? narrow_beams(kGroupRows) : RB;
+    // than a narrow unit takes; also where states are to be few: beams'
+    // blocks beside their segment's take no state of their own).
+    const int32_t most = wide_mode && !P.few_states ? narrow_beams(kGroupRows) : RB;
     for (int32_t s = 0; s < nseg; ++s) wide[s] = (m.seg_beam_end[s] - m.seg_beam_begin[s]) > most;
     items.clear();
     for (auto& t : top) {
@@ -485,6 +486,17 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     const int32_t slots = S > 0 ? *std::max_element(slot_cnt.begin(), slot_cnt.end()) : 0;
     return kMergeFixedUs + kMergeSlotUs * slots;
   };
+  // Whether the templates' partial states outgrow the library's own scratch
+  // array (counted in whole rows, with room for the two arrays' alignment).
+  const double state_bytes = shape.head_dim * (shape.kv_bytes == 4 ? 4.0 : 2.0) + 4 * kPartMl;
+  auto outgrows = [&](double rows_per_head) {
+    return rows_per_head * hkv * state_bytes + 512 > static_cast<double>(kScratchBytes);
+  };
+  auto over = [&](const std::vector<Tmpl>& t) {
+    double rows = 0;
+    for (const Tmpl& x : t) rows += static_cast<double>(x.hi - x.lo) * g;
+    return outgrows(rows);
+  };
   // One search at the current RW: fills tm, bins, ngroups and the plan's
   // target, work and chaining; returns the modelled time.
   auto search = [&]() {
@@ -536,7 +548,8 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       make_templates(T, cand, cg);
       if (static_cast<int32_t>(cand.size()) > fit_units && 4 * S < nbins / hkv && est >= 0) return;
       const double e = place(cand, cg, cbins) + merge_us(cand);
-      if (est >= 0 && e >= est) return;
+      const bool fit = P.few_states && !over(cand), had_fit = P.few_states && !over(tm);
+      if (est >= 0 && (fit != had_fit ? had_fit : e >= est)) return;
       est = e;
       P.chained = static_cast<int32_t>(cand.size()) * hkv > nbins;
       tm.swap(cand);
@@ -561,6 +574,10 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   //   us per call against 24.2 with 32) and wide units of up to 192 rows, or
   //   256.
   // A warm re-plan keeps the earlier plan's caps.
+  // Smaller units write more partial states. The call that keeps them in the
+  // library's scratch array refuses a plan that outgrows it, so a plan that
+  // does is replaced by one of larger units where that fits (512 to 3072
+  // beams: up to 1.3 times the bytes without this rule).
   auto set_caps = [&](int32_t wide_rows, int32_t narrow_rows) {
     P.wide_rows = wide_rows;
     P.narrow_rows = narrow_rows;
@@ -569,26 +586,33 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     list_items();
   };
   if (warm && warm->target_us > 0 && warm->work_us > 0 && warm->wide_rows > 0) {
+    P.few_states = warm->few_states;
     set_caps(warm->wide_rows, warm->narrow_rows);
     search();
+    if (over(tm) && !outgrows(warm->rows_per_head)) warm = nullptr;
   } else {
+    warm = nullptr;
+  }
+  if (!warm) {
+    P.few_states = false;
     set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming ? kGroupRows : kMaxRows);
     double best = search();
-    // Runs the search at another wide cap and keeps it if it models faster
-    // than the plan at hand, else restores that plan.
-    auto try_caps = [&](int32_t wide_rows) {
+    // Runs the search at other caps and keeps its plan if keep (of its
+    // modelled time) says so, else restores the plan at hand.
+    auto try_caps = [&](int32_t wide_rows, int32_t narrow_rows, auto keep) {
       std::vector<Tmpl> tm0 = tm;
       std::vector<std::vector<Work>> bins0 = bins;
-      const int32_t ngroups0 = ngroups, wide0 = P.wide_rows;
+      const int32_t ngroups0 = ngroups, wide0 = P.wide_rows, narrow0 = P.narrow_rows;
       const double target0 = P.target_us, work0 = P.work_us;
       const bool chained0 = P.chained;
-      set_caps(wide_rows, P.narrow_rows);
+      set_caps(wide_rows, narrow_rows);
       const double alt = search();
-      if (alt < kCapGain * best) {
+      if (keep(alt)) {
         best = alt;
         return;
       }
-      set_caps(wide0, P.narrow_rows);
+      P.few_states = false;
+      set_caps(wide0, narrow0);
       tm.swap(tm0);
       bins.swap(bins0);
       ngroups = ngroups0;
@@ -604,7 +628,11 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       const int32_t G = m.seg_beam_end[s] - m.seg_beam_begin[s];
       if (wide[s] && (G + RW - 1) / RW != (G + most - 1) / most) chunks_differ = true;
     }
-    if (chunks_differ) try_caps(kMaxWideRows);
+    if (chunks_differ) try_caps(kMaxWideRows, P.narrow_rows, [&](double us) { return us < kCapGain * best; });
+    if (over(tm)) {
+      P.few_states = true;
+      try_caps(kMaxWideRows, kMaxRows, [&](double) { return !over(tm); });
+    }
   }
 
   // ---- partial rows and merge lists ----------------------------------------

@@ -3,6 +3,7 @@
 // host compiler.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 
 namespace tts {
@@ -83,6 +84,8 @@ static_assert(sizeof(UnitRec) == 32 + 4 * kMaxWideBeams + 16 * kMaxEntries, "Uni
 // D = 128; generally (D / 4) q + 4 t + j) holds dimension 16 t + 4 q + j,
 // the order in which the attention kernel's lanes hold the row.
 constexpr int kPartMl = 4;  // floats per row of part_ml: m, l, z, 0
+// Bytes of the library's own array for these (the allocation-free call).
+constexpr size_t kScratchBytes = size_t{64} << 20;
 
 struct AttnParams {
   const void* q;

@@ -133,3 +133,36 @@ def test_row_caps_are_chosen_per_batch():
     r = unit_rows("7b64_balanced", wide=True)
     assert r and max(r) <= 128
     assert max(unit_rows("1p5b16", wide=False)) <= 42
+
+
+def test_states_fit_the_scratch_array():
+    """A batch of 3072 beams whose plan of the fastest units writes more than the 64 MiB of partial states that the
+    allocation-free call holds: the plan taken writes less. (Shared segments of 33 to 64 rows are units of their own
+    in the fastest plan, one more state for each of their beams.)"""
+    reqs, beams, g, hkv, d = 48, 64, 7, 4, 128
+    nxt = 0
+    tables = np.full((reqs * beams, 64), -1, np.int32)
+    lens = np.zeros(reqs * beams, np.int32)
+
+    def fresh(n):
+        nonlocal nxt
+        nxt += n
+        return list(range(nxt - n, nxt))
+
+    for r in range(reqs):  # a prompt, groups of 8 beams, pairs, private blocks
+        prompt = fresh(12)
+        for a in range(beams // 8):
+            mid = fresh(5)
+            for p in range(4):
+                pair = fresh(4)
+                for k in range(2):
+                    b = r * beams + a * 8 + p * 2 + k
+                    ids = prompt + mid + pair + fresh(3)
+                    tables[b, : len(ids)] = ids
+                    lens[b] = 16 * len(ids) - 5
+    offs = np.arange(reqs + 1, dtype=np.int32) * beams
+    desc = tts.make_desc(g * hkv, hkv, d, BS, "bf16", "bf16")
+    rows, _ = tts.tts_plan_units_host(offs, tables, lens, BS, nxt, desc, 256)
+    own = rows[rows[:, 2] == 0]
+    states = len(np.unique(own[:, 0].astype(np.int64) * len(lens) + own[:, 3]))
+    assert states * g * hkv * (2 * d + 16) <= 64 << 20
