@@ -380,6 +380,63 @@ __device__ __forceinline__ void mask_v(VOps<D, KV>& o, int lq, int valid0, int v
   }
 }
 
+// A row's state from those that ns of up to kN waves published in LDS
+// (slot(k): state k of the tile, rows of D + 4 floats, then m and l), summed
+// in order: this thread's elements (D / 16) c .. in stored order, the
+// maximum and the sum. ns = 0: an empty state.
+template <int D, int KV, int kN, typename Slot>
+__device__ __forceinline__ void combine_row(Slot slot, int ns, int row, int c, f32x4 (&o)[D / 64], float& mx,
+                                            float& l) {
+  using G = Geo<D, KV>;
+  constexpr int kEl = D / 16, kHalf = kN < 4 ? kN : 4;
+  // Stored elements (D / 16) c .. are dimensions 16 t + 4 q + j.
+  const int q4 = c >> 2, tt = (c & 3) * (kEl / 4);
+  // (Past the last state the reads repeat the first place; what they bring
+  // is not used.)
+  float mw[kN], lw[kN];
+  f32x4 ov[kHalf][kEl / 4];
+  auto read_states = [&](int k0) {
+#pragma unroll
+    for (int k = 0; k < kHalf; ++k) {
+      const float* x = slot(k0 + k < ns ? k0 + k : 0);
+#pragma unroll
+      for (int e = 0; e < kEl / 4; ++e)
+        ov[k][e] = *reinterpret_cast<const f32x4*>(x + row * G::comb_row + 16 * (tt + e) + 4 * q4);
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    const float* x = slot(k < ns ? k : 0) + kTok * G::comb_row + row;
+    mw[k] = x[0];
+    lw[k] = x[kTok];
+  }
+  read_states(0);
+  mx = kNegInf;
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    if (k >= ns) {
+      mw[k] = kNegInf;
+      lw[k] = 0.f;
+    }
+    mx = fmaxf(mx, mw[k]);
+  }
+  l = 0.f;
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    mw[k] = mw[k] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mw[k] - mx);  // now the weight
+    l += lw[k] * mw[k];
+  }
+#pragma unroll
+  for (int e = 0; e < kEl / 4; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    if (k >= ns) break;  // uniform
+    if (k == kHalf) read_states(kHalf);
+#pragma unroll
+    for (int e = 0; e < kEl / 4; ++e) o[e] += ov[k % kHalf][e] * mw[k];
+  }
+}
+
 // Query rows of the unit in LDS (B operand of S^T = K Q^T): row r is D
 // elements (bf16, or fp32 for fp32 caches), its 16-byte columns XOR-swizzled
 // by the row so that the 16 lanes of a column read distinct banks.
@@ -1590,50 +1647,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         const int c16 = ln, rrow = (tid >> 4) & 15, row = 16 * r + rrow;
         const int q4 = c16 >> 2, tt = (c16 & 3) * (kEl / 4);
         const int w0 = group_first(ws, r / kNt), ns = nsrc[r / kNt], ti = r % kNt;
-        // (Past the last state the reads repeat the first place; what they
-        // bring is not used.)
-        float mw[kWaves], lw[kWaves], mx = kNegInf;
-        f32x4 ov[kWaves / 2][kEl / 4];
-        auto read_states = [&](int k0) {
-#pragma unroll
-          for (int k = 0; k < kWaves / 2; ++k) {
-            const float* c = comb_slot(w0 + (k0 + k < ns ? k0 + k : 0), ti);
-#pragma unroll
-            for (int e = 0; e < kEl / 4; ++e)
-              ov[k][e] = *reinterpret_cast<const f32x4*>(c + rrow * G::comb_row + 16 * (tt + e) + 4 * q4);
-          }
-        };
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-          const float* c = comb_slot(w0 + (k < ns ? k : 0), ti) + kTok * G::comb_row + rrow;
-          mw[k] = c[0];
-          lw[k] = c[kTok];
-        }
-        read_states(0);
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-          if (k >= ns) {
-            mw[k] = kNegInf;
-            lw[k] = 0.f;
-          }
-          mx = fmaxf(mx, mw[k]);
-        }
-        float l = 0.f;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-          mw[k] = mw[k] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mw[k] - mx);  // now the weight
-          l += lw[k] * mw[k];
-        }
+        float mx, l;
         f32x4 o[kEl / 4];
-#pragma unroll
-        for (int e = 0; e < kEl / 4; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-          if (k >= ns) break;  // uniform (no state at all: the row's beam holds no block here)
-          if (k == kWaves / 2) read_states(kWaves / 2);
-#pragma unroll
-          for (int e = 0; e < kEl / 4; ++e) o[e] += ov[k % (kWaves / 2)][e] * mw[k];
-        }
+        combine_row<D, KV, kWaves>([&](int k) { return comb_slot(w0 + k, ti); }, ns, rrow, c16, o, mx, l);
         const bool bad = ((bad_rows >> row) & 1ull) != 0;
         const float inv = l > 0.f ? 1.f / l : 0.f;
         if (paged && p.paged_nsplit == 1) {
@@ -1668,6 +1684,161 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     if (nu_rows <= 0) break;
     rec_idx = unext;
     u = nu;
+  }
+}
+
+// ---- the paged path, up to 16 query heads per KV head ------------------------
+// One workgroup of four waves per (split of up to 64 blocks, KV head, beam):
+// one row tile, query rows held in registers, each wave streaming its share
+// of the pairs. Three workgroups share a compute unit (at most 168 registers
+// and 36 KB of LDS each), so that one's round trips to the length, the table
+// and its first blocks run beside another's streaming. The units are ordered
+// by (split, KV head) with the beams next to each other and dealt to the
+// XCDs in eight contiguous runs: beams of one prefix read its blocks through
+// one L2 at about the same time. Paged call on the 7B 64-beam tree: 87 ->
+// 51 us (eight waves, one workgroup per compute unit, splits next to each
+// other), 10 TB/s of logical KV.
+constexpr int kPagedWaves = 4;
+constexpr int kPagedRows = 16;
+constexpr int kXcds = 8;
+
+template <int D, int KV>
+__global__ __launch_bounds__(64 * kPagedWaves, KV == kKvF32 && D == 128 ? 2 : 3) void paged_kernel(AttnParams p) {
+  using G = Geo<D, KV>;
+  __shared__ __attribute__((aligned(16))) float comb[kPagedWaves * G::comb_floats];
+  const unsigned total = static_cast<unsigned>(p.num_seqs) * p.hkv * p.paged_nsplit;
+  const unsigned at = blockIdx.x % kXcds * ((total + kXcds - 1) / kXcds) + blockIdx.x / kXcds;
+  if (at >= total) return;
+  const int unit = static_cast<int>(at);
+  const int b = unit % p.num_seqs, kvh = unit / p.num_seqs % p.hkv, split = unit / p.num_seqs / p.hkv;
+  const int wave = rfl(static_cast<int>(threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63, ln = lane & 15, lq = lane >> 4;
+  const size_t blk_stride = static_cast<size_t>(p.hkv) * G::blk_bytes;
+  const unsigned char* kbase = static_cast<const unsigned char*>(p.k_cache) + kvh * G::blk_bytes;
+  const unsigned char* vbase = static_cast<const unsigned char*>(p.v_cache) + kvh * G::blk_bytes;
+  // Split j covers blocks [j * per, (j + 1) * per) of the beam (per <= 64).
+  const int per = (p.paged_max_len + kTok * p.paged_nsplit - 1) / (kTok * p.paged_nsplit);
+  const int j = split * per + lane;
+  // Length and query rows together; the table only up to the length.
+  const int L = p.seq_lens[b];
+  QFrag<D, KV> q;
+  {
+    constexpr int kRowBytes = D * (KV == kKvF32 ? 4 : 2);
+    const unsigned char* row = static_cast<const unsigned char*>(p.q) +
+                               (static_cast<int64_t>(b) * p.hq + kvh * p.g + (ln < p.g ? ln : 0)) * kRowBytes;
+#pragma unroll
+    for (int i = 0; i < KOps<D, KV>::kk; ++i)
+      q.q[i] = *reinterpret_cast<const typename KOps<D, KV>::T*>(row + (4 * i + lq) * 16);
+  }
+  int nb = (L + kTok - 1) / kTok;
+  bool bad = false;
+  if (L < 0 || L > p.paged_max_len || nb > p.max_blocks) {
+    bad = true;
+    nb = 0;
+  }
+  int n = nb - split * per;
+  n = n < 0 ? 0 : (n < per ? n : per);
+  int id = 0, v = 0;
+  if (lane < n) {
+    id = p.block_tables[static_cast<int64_t>(b) * p.max_blocks + j];
+    v = L - j * kTok;
+    v = v < kTok ? v : kTok;
+  }
+  if (lane >= n || id < 0 || id >= p.num_blocks) {
+    bad |= lane < n;
+    id = 0;
+    v = 0;
+  }
+  bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+  if (p.num_blocks <= 0) n = 0;  // no block to read at all
+  Window win;
+  win.id = id;
+  win.w = win_word(0, p.g, v);
+  win.ks = 1.f;
+  win.vs = 1.f;
+  if constexpr (KV == kKvFp8) {
+    if (v > 0) {
+      win.ks = p.k_scale[id];
+      win.vs = p.v_scale[id];
+    }
+  }
+  const int np = (n + 1) >> 1;
+  RowState<D> st;
+  float m_exact = 0.f;
+  for (int attempt = 0;; ++attempt) {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) st.o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    st.m = m_exact;
+    st.l = 0.f;
+    st.seen = kNegInf;
+    Frags<D, KV> f;
+    for (int pp = wave; pp < np; pp += kPagedWaves) {
+      issue_pair<D, KV>(f, win, n, pp, kbase, vbase, blk_stride, ln, lq);
+      const int i0 = 2 * pp, i1 = 2 * pp + 1;
+      const bool has1 = i1 < n;
+      PairInfo pi;
+      pi.v0 = win_valid(rl(win.w, i0));
+      pi.v1 = has1 ? win_valid(rl(win.w, i1)) : 0;
+      pi.a0 = pi.a1 = 0;
+      pi.e0 = pi.e1 = kPagedRows;  // rows past g repeat row 0 and are not written
+      pi.ks0 = pi.ks1 = p.scale_log2;
+      pi.vs0 = pi.vs1 = 1.f;
+      if constexpr (KV == kKvFp8) {
+        pi.ks0 = p.scale_log2 * rlf(win.ks, i0);
+        pi.vs0 = rlf(win.vs, i0);
+        pi.ks1 = has1 ? p.scale_log2 * rlf(win.ks, i1) : pi.ks0;
+        pi.vs1 = has1 ? rlf(win.vs, i1) : pi.vs0;
+      }
+      if (pi.v0 <= 0 && pi.v1 <= 0) continue;
+      const Scores s = tile_scores<D, KV>(k_ops<D, KV>(f), q);
+      const Probs<KV> pr = tile_probs<D, KV>(s, st, pi, 0, ln, lq);
+      VOps<D, KV> vo = v_ops<D, KV>(f);
+      if (pi.v0 < kTok || pi.v1 < kTok) mask_v<D, KV>(vo, lq, pi.v0, pi.v1);
+      tile_values<D, KV>(vo, pr, st);
+    }
+    if (attempt > 0) break;
+    const float mx = xlane_max16(st.seen);
+    const bool redo = mx > kRefWindow || (mx < -kRefWindow && mx != kNegInf);
+    m_exact = mx == kNegInf ? 0.f : mx;
+    if (__builtin_amdgcn_ballot_w64(redo) == 0) break;
+  }
+  // The waves' states through LDS, sixteen threads to a row (as in
+  // attn_kernel).
+  auto slot = [&](int w) { return comb + w * G::comb_floats; };
+  st.l = xlane_sum16(st.l);
+  if (!(st.l > 0.f)) st.m = kNegInf;
+  if (wave < np) {
+    float* c = slot(wave);
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+      *reinterpret_cast<f32x4*>(c + ln * G::comb_row + 16 * dt + 4 * lq) = st.o[dt];
+    if (lq == 0) {
+      c[kTok * G::comb_row + ln] = st.m;
+      c[kTok * G::comb_row + kTok + ln] = st.l;
+    }
+  }
+  __syncthreads();
+  constexpr int kEl = D / 16;
+  const int row = static_cast<int>(threadIdx.x) >> 4;
+  float mx, l;
+  f32x4 o[kEl / 4];
+  combine_row<D, KV, kPagedWaves>(slot, np < kPagedWaves ? np : kPagedWaves, row, ln, o, mx, l);
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  const float qnan = __builtin_nanf("");
+  if (p.paged_nsplit == 1) {
+    // Whole sequence in this unit: the normalised result.
+    if (row < p.g) {
+      float* orow = p.out + (static_cast<int64_t>(b) * p.hq + kvh * p.g + row) * D;
+#pragma unroll
+      for (int e = 0; e < kEl / 4; ++e) {
+        f32x4 x = o[e] * inv;
+        if (bad) x = f32x4{qnan, qnan, qnan, qnan};
+        *reinterpret_cast<f32x4*>(orow + 16 * ((ln & 3) * (kEl / 4) + e) + 4 * (ln >> 2)) = x;
+      }
+    }
+  } else {
+    const int64_t prow = (static_cast<int64_t>(b) * p.paged_nsplit + split) * p.hq + kvh * p.g + row;
+    store_partial_row<D, KV>(p.part_o, p.part_ml, prow, o, bad ? qnan : mx, l, inv, ln, row < p.g);
   }
 }
 
@@ -1815,7 +1986,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
 
 template <int D, int KV>
 static hipError_t launch_attn_t(const AttnParams& p, int grid, hipStream_t stream) {
-  if (p.recs == nullptr)
+  // (More than 16 query heads per KV head: several row tiles.)
+  if (p.recs == nullptr && p.g <= kPagedRows)
+    hipLaunchKernelGGL((paged_kernel<D, KV>), dim3((static_cast<unsigned>(grid) + kXcds - 1) / kXcds * kXcds),
+                       dim3(64 * kPagedWaves), 0, stream, p);
+  else if (p.recs == nullptr)
     hipLaunchKernelGGL((attn_kernel<D, KV, false, true>), dim3(grid), dim3(kThreads), 0, stream, p);
   else if (p.two_windows)
     hipLaunchKernelGGL((attn_kernel<D, KV, true, false>), dim3(grid), dim3(kThreads), 0, stream, p);
