@@ -1292,7 +1292,10 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
           else
             run(std::integral_constant<int, 0>{});
           if (attempt == 0) TTS_PROF_MARK(1, rec_idx);
-          if (attempt > 0) break;
+          if (attempt > 0) {
+            if (halves) __syncthreads();  // every wave is done with the stages (the vote's barrier, after the first)
+            break;
+          }
           bool redo = false;
 #pragma unroll
           for (int i = 0; i < kWideTiles; ++i) {
@@ -1313,8 +1316,9 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
         }
         // Halves: each wave hands one of its tiles to the wave that shares its
         // rows and adds that wave's other tile: half 0 ends with tile w % 4,
-        // half 1 with w % 4 + 4. (The vote's barrier is past the last read of
-        // the stages.) Lane order, one 16-byte column per 16 dims.
+        // half 1 with w % 4 + 4. (The area is the stages': after either
+        // attempt a barrier lies between their last read and these stores.)
+        // Lane order, one 16-byte column per 16 dims.
         if (halves) {
           auto fold_at = [&](int w) { return comb + w * (16 * (D + 8)); };
           auto give = [&](RowState<D>& x) {

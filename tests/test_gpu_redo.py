@@ -157,3 +157,39 @@ def test_redo_prompt_far_above_tails(kind):
     print(f"prompt above tails {kind}: prefix {_err(ox, ref):.2e} paged {_err(op, ref):.2e}", flush=True)
     assert np.isfinite(ox).all() and np.isfinite(op).all()
     assert _err(ox, ref) <= TOL and _err(op, ref) <= TOL
+
+
+def _halves_batch(d, kv):
+    """24 requests of 5, 9 or 18 beams of seven heads under a shared prompt of 5 to 8 or 13 to 16 full blocks."""
+    specs = tuple(ReqSpec(beams=b, branch=1, prompt=(16 * n + 5, 16 * n + 5), step=(1, 20), max_len=1 << 20,
+                          max_iters=1, snapshot="none")
+                  for n in (5, 6, 7, 8, 13, 14, 15, 16) for b in (5, 9, 18))
+    return make_workload(WorkloadConfig("halves", AttnShape(28, 4, d, 16, "bf16", kv), specs), 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_redo_units_of_two_halves(kv, d):
+    """Wide units of up to eight row tiles, whose halves take alternate pairs and exchange tiles at the end, all
+    computed twice (queries x35): 3, 4, 7 and 8 pairs, so that the last step holds one pair or two, in either stage
+    buffer, with and without a last block."""
+    wl = _halves_batch(d, kv)
+    _, rows = _has_wide_units(wl)
+    found = set()
+    for u in np.unique(rows[(rows[:, 6] & 8) != 0, 0]):
+        of = rows[rows[:, 0] == u]
+        blocks, tiles = len(np.unique(of[:, 4])), -(-len(np.unique(of[:, 3])) * wl.shape.group // 16)
+        if tiles <= 8:
+            found.add((-(-blocks // 2), blocks % 2))
+    assert found >= {(n, odd) for n in (3, 4, 7, 8) for odd in (0, 1)}
+    wl = dataclasses.replace(wl, q=bf16_bits(35.0 * _bf16_f32(wl.q)))
+    if kv == "bf16":
+        assert min(_row_max_log2(wl, b, 1.0 / np.sqrt(d)) for b in range(wl.num_seqs)) > 64.0
+    ref = oracle_attn_workload(wl)
+    x = to_device(wl)
+    pref = PrefixAttention(x, wl.req_seq_offsets, wl.block_tables, wl.seq_lens, wl.num_blocks)
+    first = pref().cpu().numpy()
+    print(f"redo halves {kv} D {d}: prefix {_err(first, ref):.2e}", flush=True)
+    assert np.isfinite(first).all() and _err(first, ref) <= (TOL if kv == "bf16" else 2 * TOL)
+    for _ in range(20):
+        assert np.array_equal(pref().cpu().numpy(), first)
