@@ -98,15 +98,23 @@ struct CostModel {
   double wide_us(int blocks, int rows) const { return kWideFixedUs + blocks * wide_block_us(rows); }
 };
 
+// A unit of one KV head: a run [a, b) of the narrow list's items, or (seg >=
+// 0) of the blocks of a segment that is cut into units of its own. Its
+// entries are written out only for the plan that is taken (Entries).
 struct Tmpl {
   int32_t lo = 0, hi = 0;  // beam positions [lo, hi)
   int32_t mode = kModeNarrow;
+  int32_t seg = -1;
+  int32_t a = 0, b = 0;
+  double cost = 0;
+  int32_t group = -1;  // units of a segment: index of their piece
+};
+
+struct Entries {
   std::vector<int32_t> ids;
   std::vector<uint32_t> info;
   int32_t nstatic = 0;   // narrow: static entries of the first window; wide: all entries
   int32_t nstatic2 = 0;  // narrow: entries of the second window (after the extension entries)
-  double cost = 0;
-  int32_t group = -1;  // wide units: index of their piece
 };
 
 struct NItem {
@@ -122,15 +130,11 @@ struct Work {
 };
 
 // Which of a unit's beams (t.lo + i) it writes partial states for: all of
-// a wide unit's; a narrow unit's whose rows some entry covers.
-void touched_beams(const Tmpl& t, int32_t g, std::vector<char>* out) {
-  const int32_t nb = t.hi - t.lo;
-  out->assign(nb, t.mode == kModeWide ? 1 : 0);
-  for (size_t k = 0; t.mode == kModeNarrow && k < t.ids.size(); ++k) {
-    const uint32_t inf = t.info[k];
-    const int32_t r0 = inf & 63, r1 = ((inf >> 6) & 63) + 1;
-    for (int32_t i = r0 / g; i < (r1 + g - 1) / g && i < nb; ++i) (*out)[i] = 1;
-  }
+// a segment's unit; of a narrow run those that some item covers.
+void touched_beams(const Tmpl& t, const std::vector<NItem>& items, std::vector<char>* out) {
+  out->assign(t.hi - t.lo, t.seg >= 0 ? 1 : 0);
+  for (int32_t k = t.a; t.seg < 0 && k < t.b; ++k)
+    for (int32_t i = items[k].p0 - t.lo; i < items[k].p1 - t.lo; ++i) (*out)[i] = 1;
 }
 
 }  // namespace
@@ -253,9 +257,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // plus the merge of its pieces' states (else the fastest). The narrow list
   // is cut greedily into units that fit T.
   auto span_of = [&](int32_t blocks, int32_t rows) { return rows > kGroupRows ? blocks : 0; };
-  auto make_templates = [&](double T, std::vector<Tmpl>& tm, int32_t& ngroups) {
+  auto make_templates = [&](double T, std::vector<Tmpl>& tm) {
     tm.clear();
-    ngroups = 0;
+    int32_t ngroups = 0;
     for (int32_t s = 0; s < nseg; ++s) {  // preorder: ancestors first
       if (!wide[s]) continue;
       const int32_t bb = m.seg_beam_begin[s], G = m.seg_beam_end[s] - bb;
@@ -297,89 +301,88 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
           t.hi = bb + static_cast<int32_t>(static_cast<int64_t>(G) * (c + 1) / C);
           const int32_t rows = (t.hi - t.lo) * g;
           t.mode = best.mode;
-          for (int32_t k = a; k < e; ++k) {
-            t.ids.push_back(seg_block(s, k));
-            t.info.push_back(t.mode == kModeWide ? 0u : ent_info(0, rows, bs, 0u));
-          }
-          t.nstatic = e - a;
+          t.seg = s;
+          t.a = a;
+          t.b = e;
           t.cost = t.mode == kModeWide ? cm.wide_us(e - a, rows) : cm.narrow_us(e - a, span_of(e - a, rows), rows);
           t.group = ngroups;
-          tm.push_back(std::move(t));
+          tm.push_back(t);
         }
         ++ngroups;
       }
     }
     Tmpl cur;
-    std::vector<NItem> pend, ext;  // the open unit's static and extension items
-    int32_t nblk = 0, nspan = 0;
+    // The open unit: its static items, those with rows of both wave groups,
+    // and the LIVE and extension items.
+    int32_t nblk = 0, nspan = 0, nlive_ext = 0;
     auto spans = [&](const NItem& it, int32_t lo) {
       return (it.flags & kEntExt) == 0 && (it.p0 - lo) * g < kGroupRows && (it.p1 - lo) * g > kGroupRows;
     };
-    // A unit's entries: the first window holds its LIVE entries, static
-    // entries up to 64 with the extension entries, which come last; the
-    // second window the remaining static entries (the order of a unit's
-    // blocks does not change its result beyond rounding).
     auto flush = [&]() {
-      if (pend.empty() && ext.empty()) return;
-      auto push = [&](const NItem& it) {
-        cur.ids.push_back(it.id);
-        cur.info.push_back(ent_info((it.p0 - cur.lo) * g, (it.p1 - cur.lo) * g, it.valid, it.flags));
-      };
-      const int32_t room1 = kMaxEntries - static_cast<int32_t>(ext.size());
-      int32_t nlive = 0;
-      for (const NItem& it : pend) nlive += (it.flags & kEntLive) ? 1 : 0;
-      int32_t plain1 = room1 - nlive;  // plain static entries the first window takes
-      std::vector<const NItem*> second;
-      for (const NItem& it : pend) {
-        if ((it.flags & kEntLive) || plain1 > 0) {
-          if (!(it.flags & kEntLive)) --plain1;
-          push(it);
-        } else {
-          second.push_back(&it);
-        }
-      }
-      cur.nstatic = static_cast<int32_t>(cur.ids.size());
-      for (const NItem& it : ext) {
-        cur.ids.push_back(it.p0 - cur.lo);
-        cur.info.push_back(ent_info((it.p0 - cur.lo) * g, (it.p1 - cur.lo) * g, 1, kEntExt));
-      }
-      for (const NItem* it : second) push(*it);
-      cur.nstatic2 = static_cast<int32_t>(second.size());
-      cur.cost = cm.narrow_us(cur.nstatic + cur.nstatic2, nspan, (cur.hi - cur.lo) * g);
-      tm.push_back(std::move(cur));
-      cur = Tmpl();
-      pend.clear();
-      ext.clear();
-      nblk = 0;
-      nspan = 0;
+      if (cur.b == cur.a) return;
+      cur.cost = cm.narrow_us(nblk, nspan, (cur.hi - cur.lo) * g);
+      tm.push_back(cur);
+      cur.a = cur.b;
+      nblk = nspan = nlive_ext = 0;
     };
-    for (const NItem& it : items) {
-      const bool is_ext = (it.flags & kEntExt) != 0;
-      if (!pend.empty() || !ext.empty()) {
+    for (int32_t k = 0; k < static_cast<int32_t>(items.size()); ++k) {
+      const NItem& it = items[k];
+      const int32_t blk = (it.flags & kEntExt) ? 0 : 1, live = (it.flags & (kEntLive | kEntExt)) ? 1 : 0;
+      if (cur.b > cur.a) {
         const int32_t lo = std::min(cur.lo, it.p0), hi = std::max(cur.hi, it.p1);
-        int32_t nlive = 0;
-        for (const NItem& x : pend) nlive += (x.flags & kEntLive) ? 1 : 0;
-        const int32_t live_ext = nlive + static_cast<int32_t>(ext.size()) +
-                                 ((it.flags & (kEntLive | kEntExt)) ? 1 : 0);
-        const bool fits = hi - lo <= RB && static_cast<int32_t>(pend.size() + ext.size()) + 1 <= kMaxUnitEntries &&
-                          live_ext <= kMaxEntries && cm.narrow_us(nblk + (is_ext ? 0 : 1), nspan + (spans(it, lo) ? 1 : 0), (hi - lo) * g) <= T;
+        const bool fits = hi - lo <= RB && cur.b - cur.a + 1 <= kMaxUnitEntries && nlive_ext + live <= kMaxEntries &&
+                          cm.narrow_us(nblk + blk, nspan + (spans(it, lo) ? 1 : 0), (hi - lo) * g) <= T;
         if (!fits) flush();
       }
-      if (pend.empty() && ext.empty()) {
+      if (cur.b == cur.a) {
         cur.lo = it.p0;
         cur.hi = it.p1;
       }
       cur.lo = std::min(cur.lo, it.p0);
       cur.hi = std::max(cur.hi, it.p1);
-      if (is_ext) {
-        ext.push_back(it);
-      } else {
-        pend.push_back(it);
-        ++nblk;
-        nspan += spans(it, cur.lo) ? 1 : 0;
-      }
+      cur.b = k + 1;
+      nblk += blk;
+      nspan += spans(it, cur.lo) ? 1 : 0;
+      nlive_ext += live;
     }
     flush();
+  };
+
+  // A unit's entries: the first window holds its LIVE entries, static
+  // entries up to 64 with the extension entries, which come last; the
+  // second window the remaining static entries (the order of a unit's
+  // blocks does not change its result beyond rounding).
+  auto write_entries = [&](const Tmpl& t, Entries* out) {
+    Entries& x = *out;
+    x.ids.clear();
+    x.info.clear();
+    if (t.seg >= 0) {
+      const uint32_t info = t.mode == kModeWide ? 0u : ent_info(0, (t.hi - t.lo) * g, bs, 0u);
+      for (int32_t k = t.a; k < t.b; ++k) x.ids.push_back(seg_block(t.seg, k));
+      x.info.assign(x.ids.size(), info);
+      x.nstatic = t.b - t.a;
+      x.nstatic2 = 0;
+      return;
+    }
+    auto push = [&](const NItem& it) {
+      const bool is_ext = (it.flags & kEntExt) != 0;
+      x.ids.push_back(is_ext ? it.p0 - t.lo : it.id);
+      x.info.push_back(ent_info((it.p0 - t.lo) * g, (it.p1 - t.lo) * g, it.valid, it.flags));
+    };
+    int32_t room = kMaxEntries;  // plain static entries the first window takes
+    for (int32_t k = t.a; k < t.b; ++k) room -= (items[k].flags & (kEntLive | kEntExt)) ? 1 : 0;
+    int32_t plain = 0;
+    for (int32_t k = t.a; k < t.b; ++k) {
+      if (items[k].flags & kEntExt) continue;
+      if ((items[k].flags & kEntLive) || plain++ < room) push(items[k]);
+    }
+    x.nstatic = static_cast<int32_t>(x.ids.size());
+    for (int32_t k = t.a; k < t.b; ++k)
+      if (items[k].flags & kEntExt) push(items[k]);
+    plain = 0;
+    for (int32_t k = t.a; k < t.b; ++k)
+      if (!(items[k].flags & (kEntLive | kEntExt)) && plain++ >= room) push(items[k]);
+    x.nstatic2 = std::max(0, plain - room);
   };
 
   // ---- placement: groups -> XCDs -> workgroups ------------------------------
@@ -387,29 +390,22 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // KV head) form a group that stays on one XCD, so they share its L2;
   // groups go to the XCDs longest first, then each XCD's units to its
   // workgroups longest first. Returns the largest workgroup load.
-  auto place = [&](const std::vector<Tmpl>& tm, int32_t ngroups, std::vector<std::vector<Work>>& bins) {
-    struct Group {
-      double cost = 0;
-      std::vector<Work> units;
-    };
-    std::vector<Group> groups;
-    std::vector<int32_t> gidx(static_cast<size_t>(ngroups) * hkv, -1);
+  // bins: each workgroup's units, or null for the load alone.
+  struct Group {  // templates [t0, t1) of one KV head
+    int32_t t0, t1, kvh;
+    double cost;
+  };
+  std::vector<Group> groups;
+  auto place = [&](const std::vector<Tmpl>& tm, std::vector<std::vector<Work>>* bins) {
+    groups.clear();
     for (int32_t kvh = 0; kvh < hkv; ++kvh) {
-      for (size_t t = 0; t < tm.size(); ++t) {
-        int32_t gi;
-        if (tm[t].group >= 0) {
-          int32_t& slot = gidx[static_cast<size_t>(tm[t].group) * hkv + kvh];
-          if (slot < 0) {
-            slot = static_cast<int32_t>(groups.size());
-            groups.emplace_back();
-          }
-          gi = slot;
+      for (int32_t t = 0; t < static_cast<int32_t>(tm.size()); ++t) {
+        if (tm[t].group >= 0 && t > 0 && tm[t].group == tm[t - 1].group) {
+          groups.back().t1 = t + 1;
+          groups.back().cost += tm[t].cost;
         } else {
-          gi = static_cast<int32_t>(groups.size());
-          groups.emplace_back();
+          groups.push_back({t, t + 1, kvh, tm[t].cost});
         }
-        groups[gi].units.push_back({static_cast<int32_t>(t), kvh, tm[t].cost});
-        groups[gi].cost += tm[t].cost;
       }
     }
     std::vector<int32_t> gorder(groups.size());
@@ -426,9 +422,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       for (int32_t k = 1; k < nx; ++k)
         if (xload[k] / xbins[k] < xload[x] / xbins[x]) x = k;
       xload[x] += groups[gi].cost;
-      for (const Work& w : groups[gi].units) xunits[x].push_back(w);
+      for (int32_t t = groups[gi].t0; t < groups[gi].t1; ++t) xunits[x].push_back({t, groups[gi].kvh, tm[t].cost});
     }
-    bins.assign(nbins, {});
+    if (bins) bins->assign(nbins, {});
     double makespan = 0;
     for (int32_t x = 0; x < nx; ++x) {
       auto& v = xunits[x];
@@ -441,14 +437,15 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
         for (size_t k = 1; k < mine.size(); ++k)
           if (load[k] < load[best]) best = k;
         load[best] += w.cost;
-        bins[mine[best]].push_back(w);
+        if (bins) (*bins)[mine[best]].push_back(w);
       }
       for (double l : load) makespan = std::max(makespan, l);
     }
     // Within a workgroup, wide units first (their chunks run concurrently on
     // the XCD's other workgroups and share its L2), then in creation order.
-    for (auto& v : bins)
-      std::stable_sort(v.begin(), v.end(), [](const Work& a, const Work& b) { return a.t < b.t; });
+    if (bins)
+      for (auto& v : *bins)
+        std::stable_sort(v.begin(), v.end(), [](const Work& a, const Work& b) { return a.t < b.t; });
     return makespan;
   };
 
@@ -462,8 +459,6 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // the merge) is taken. When even the largest units outnumber the
   // workgroups, the targets are taken around the average work.
   std::vector<Tmpl> tm;
-  std::vector<std::vector<Work>> bins;
-  int32_t ngroups = 0;
   // Units (of one KV head) that fit the workgroups one each. A batch with
   // enough beams to fill half of them at four units per beam and head gets
   // no more than that: few partial states per beam.
@@ -471,7 +466,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   if (4 * S >= fit_units / 2) fit_units = std::min(fit_units, 4 * S);
   const double target0 = kNarrowFixedUs;  // a unit's fixed part: targets scale what is above it
   auto units_at = [&](double T) {
-    make_templates(T, tm, ngroups);
+    make_templates(T, tm);
     return static_cast<int32_t>(tm.size());
   };
   std::vector<char> touched;
@@ -479,7 +474,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   auto merge_us = [&](const std::vector<Tmpl>& t) {
     slot_cnt.assign(S, 0);
     for (const Tmpl& x : t) {
-      touched_beams(x, g, &touched);
+      touched_beams(x, items, &touched);
       for (int32_t i = 0; i < x.hi - x.lo; ++i)
         if (touched[i]) ++slot_cnt[m.perm[x.lo + i]];
     }
@@ -497,8 +492,8 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     for (const Tmpl& x : t) rows += static_cast<double>(x.hi - x.lo) * g;
     return outgrows(rows);
   };
-  // One search at the current RW: fills tm, bins, ngroups and the plan's
-  // target, work and chaining; returns the modelled time.
+  // One search at the current RW: fills tm and the plan's target, work and
+  // chaining; returns the modelled time.
   auto search = [&]() {
     double est = -1;
     double work = 0;
@@ -518,10 +513,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       if (!warm->chained)
         for (int it = 0; it < 12 && units_at(T) > fit_units; ++it) T = target0 + 1.15 * (T - target0);
       units_at(T);
-      est = place(tm, ngroups, bins);
       P.target_us = T;
       P.chained = warm->chained;
-      return est;
+      return 0.0;
     }
     // Upper bound of the bisection: a few times the average work per unit,
     // raised while the units do not fit (one entry of many rows can cost
@@ -542,19 +536,15 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       base = hi - target0;
     }
     std::vector<Tmpl> cand;
-    std::vector<std::vector<Work>> cbins;
     auto try_target = [&](double T) {
-      int32_t cg = 0;
-      make_templates(T, cand, cg);
+      make_templates(T, cand);
       if (static_cast<int32_t>(cand.size()) > fit_units && 4 * S < nbins / hkv && est >= 0) return;
-      const double e = place(cand, cg, cbins) + merge_us(cand);
+      const double e = place(cand, nullptr) + merge_us(cand);
       const bool fit = P.few_states && !over(cand), had_fit = P.few_states && !over(tm);
       if (est >= 0 && (fit != had_fit ? had_fit : e >= est)) return;
       est = e;
       P.chained = static_cast<int32_t>(cand.size()) * hkv > nbins;
       tm.swap(cand);
-      bins.swap(cbins);
-      ngroups = cg;
       P.target_us = T;
     };
     if (fits)
@@ -601,8 +591,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     // modelled time) says so, else restores the plan at hand.
     auto try_caps = [&](int32_t wide_rows, int32_t narrow_rows, auto keep) {
       std::vector<Tmpl> tm0 = tm;
-      std::vector<std::vector<Work>> bins0 = bins;
-      const int32_t ngroups0 = ngroups, wide0 = P.wide_rows, narrow0 = P.narrow_rows;
+      const int32_t wide0 = P.wide_rows, narrow0 = P.narrow_rows;
       const double target0 = P.target_us, work0 = P.work_us;
       const bool chained0 = P.chained;
       set_caps(wide_rows, narrow_rows);
@@ -614,8 +603,6 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       P.few_states = false;
       set_caps(wide0, narrow0);
       tm.swap(tm0);
-      bins.swap(bins0);
-      ngroups = ngroups0;
       P.target_us = target0;
       P.work_us = work0;
       P.chained = chained0;
@@ -635,6 +622,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     }
   }
 
+  std::vector<std::vector<Work>> bins;
+  place(tm, &bins);
+
   // ---- partial rows and merge lists ----------------------------------------
   std::vector<int32_t> prow0(tm.size());
   std::vector<std::vector<int32_t>> per_beam(S);
@@ -643,7 +633,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     prow0[t] = rows;
     const int32_t nb = tm[t].hi - tm[t].lo;
     std::vector<char> touched;
-    touched_beams(tm[t], g, &touched);
+    touched_beams(tm[t], items, &touched);
     for (int32_t i = 0; i < nb; ++i)
       if (touched[i]) per_beam[m.perm[tm[t].lo + i]].push_back(rows + i * g);
     rows += nb * g;
@@ -668,42 +658,44 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // Waves of the first of a narrow unit's two wave groups (UnitRec::mode;
   // rows 0 .. 31 and the rest, for fp32 caches 0 .. 15): in proportion to
   // the block entries with rows of each group.
-  auto first_group_waves = [&](const Tmpl& t) {
+  auto first_group_waves = [&](const Tmpl& t, const Entries& x) {
     const int32_t cut = wide_mode ? kGroupRows : kGroupRows / 2;
     int32_t c0 = 0, c1 = 0;
-    for (size_t k = 0; t.mode == kModeNarrow && k < t.ids.size(); ++k) {
-      if (t.info[k] & kEntExt) continue;
-      const int32_t r0 = t.info[k] & 63, r1 = ((t.info[k] >> 6) & 63) + 1;
+    for (size_t k = 0; t.mode == kModeNarrow && k < x.ids.size(); ++k) {
+      if (x.info[k] & kEntExt) continue;
+      const int32_t r0 = x.info[k] & 63, r1 = ((x.info[k] >> 6) & 63) + 1;
       c0 += r0 < cut;
       c1 += r1 > cut;
     }
     const int32_t n = c0 + c1 > 0 ? (kUnitWaves * c0 + (c0 + c1) / 2) / (c0 + c1) : kUnitWaves / 2;
     return std::min(kUnitWaves - 1, std::max(1, n));
   };
+  Entries x;
   auto make_rec = [&](const Work& w) {
     UnitRec r{};
     const Tmpl& t = tm[w.t];
+    write_entries(t, &x);
     r.kvh = w.kvh;
     r.nrows = (t.hi - t.lo) * g;
-    r.nstatic = t.nstatic;
-    r.nent = static_cast<int32_t>(t.ids.size());
+    r.nstatic = x.nstatic;
+    r.nent = static_cast<int32_t>(x.ids.size());
     r.prow0 = prow0[w.t];
     r.next = -1;
-    r.mode = t.mode | first_group_waves(t) << 8;
+    r.mode = t.mode | first_group_waves(t, x) << 8;
     for (int32_t i = 0; i < t.hi - t.lo; ++i) r.beams[i] = m.perm[t.lo + i];
     // First window: entries [0, n1); second window: the rest.
-    const size_t n1 = t.ids.size() - static_cast<size_t>(t.mode == kModeWide ? std::max(0, t.nstatic - kMaxEntries)
-                                                                                : t.nstatic2);
-    r.nstatic2 = static_cast<int32_t>(t.ids.size() - n1);
+    const size_t n1 = x.ids.size() - static_cast<size_t>(t.mode == kModeWide ? std::max(0, x.nstatic - kMaxEntries)
+                                                                                : x.nstatic2);
+    r.nstatic2 = static_cast<int32_t>(x.ids.size() - n1);
     if (t.mode == kModeNarrow) r.nent = static_cast<int32_t>(n1);
     if (r.nstatic2 > 0) P.two_windows = true;
-    for (size_t k = 0; k < t.ids.size(); ++k) {
+    for (size_t k = 0; k < x.ids.size(); ++k) {
       if (k < n1) {
-        r.ent_id[k] = t.ids[k];
-        r.ent_info[k] = t.info[k];
+        r.ent_id[k] = x.ids[k];
+        r.ent_info[k] = x.info[k];
       } else {
-        r.ent_id2[k - n1] = t.ids[k];
-        r.ent_info2[k - n1] = t.info[k];
+        r.ent_id2[k - n1] = x.ids[k];
+        r.ent_info2[k - n1] = x.info[k];
       }
     }
     return r;
