@@ -487,11 +487,12 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   auto outgrows = [&](double rows_per_head) {
     return rows_per_head * hkv * state_bytes + 512 > static_cast<double>(kScratchBytes);
   };
-  auto over = [&](const std::vector<Tmpl>& t) {
+  auto rows_of = [&](const std::vector<Tmpl>& t) {
     double rows = 0;
     for (const Tmpl& x : t) rows += static_cast<double>(x.hi - x.lo) * g;
-    return outgrows(rows);
+    return rows;
   };
+  auto over = [&](const std::vector<Tmpl>& t) { return outgrows(rows_of(t)); };
   // One search at the current RW: fills tm and the plan's target, work and
   // chaining; returns the modelled time.
   auto search = [&]() {
@@ -575,16 +576,25 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     RW = wide_beams(wide_rows);
     list_items();
   };
+  // A warm re-plan keeps the choice too, unless the other one would now fit
+  // (judged by few_ratio): a batch that shrank gets its fastest plan back,
+  // and one whose plan outgrows the array is planned anew where larger units
+  // may fit.
   if (warm && warm->target_us > 0 && warm->work_us > 0 && warm->wide_rows > 0) {
     P.few_states = warm->few_states;
+    P.few_ratio = warm->few_ratio;
     set_caps(warm->wide_rows, warm->narrow_rows);
     search();
-    if (over(tm) && !outgrows(warm->rows_per_head)) warm = nullptr;
+    const double rows = rows_of(tm);
+    const bool anew = P.few_states ? !outgrows(rows / P.few_ratio) || (outgrows(rows) && !outgrows(warm->rows_per_head))
+                                   : outgrows(rows) && !outgrows(rows * P.few_ratio);
+    if (anew) warm = nullptr;
   } else {
     warm = nullptr;
   }
   if (!warm) {
     P.few_states = false;
+    P.few_ratio = 0;
     set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming ? kGroupRows : kMaxRows);
     double best = search();
     // Runs the search at other caps and keeps its plan if keep (of its
@@ -617,8 +627,12 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     }
     if (chunks_differ) try_caps(kMaxWideRows, P.narrow_rows, [&](double us) { return us < kCapGain * best; });
     if (over(tm)) {
+      const double rows = rows_of(tm);
       P.few_states = true;
-      try_caps(kMaxWideRows, kMaxRows, [&](double) { return !over(tm); });
+      try_caps(kMaxWideRows, kMaxRows, [&](double) {
+        P.few_ratio = rows_of(tm) / rows;
+        return !over(tm);
+      });
     }
   }
 
