@@ -480,6 +480,7 @@ tts_status tts_paged_decode_attn(const tts_attn_desc* d, int32_t num_seqs, const
     mp.hq = d->num_q_heads;
     mp.g = d->num_q_heads / d->num_kv_heads;
     mp.paged_nsplit = ns;
+    mp.q_len = 1;
     e = tts::launch_merge(mp, d->head_dim, kv_kind(d), stream);
     if (e != hipSuccess) return fail(TTS_ERR_HIP, std::string("merge launch: ") + hipGetErrorString(e));
   }

@@ -1999,39 +1999,82 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
   }
 }
 
+// A launch holds fewer than 2^32 threads; calls of more are made in runs of
+// whole beams.
+constexpr int64_t kMaxLaunchThreads = 0xFFFFFFFFll;
+
+// The paged path. (More than 16 query heads per KV head: several row tiles.)
+template <int D, int KV>
+static hipError_t launch_paged_t(AttnParams p, hipStream_t stream) {
+  const bool small = p.g <= kPagedRows;
+  const int threads = small ? 64 * kPagedWaves : kThreads;
+  const int64_t per = static_cast<int64_t>(p.hkv) * p.paged_nsplit;  // workgroups of a beam
+  const int64_t fit = kMaxLaunchThreads / threads / kXcds * kXcds / per, most = fit > 1 ? fit : 1;
+  const int64_t q_beam = static_cast<int64_t>(p.hq) * D * (KV == kKvF32 ? 4 : 2);
+  for (int64_t left = p.num_seqs; left > 0; left -= most) {
+    const int64_t n = left < most ? left : most;
+    p.num_seqs = static_cast<int32_t>(n);
+    const unsigned grid = static_cast<unsigned>(n * per);
+    if (small)
+      hipLaunchKernelGGL((paged_kernel<D, KV>), dim3((grid + kXcds - 1) / kXcds * kXcds), dim3(threads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((attn_kernel<D, KV, false, true>), dim3(grid), dim3(threads), 0, stream, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    p.q = static_cast<const char*>(p.q) + n * q_beam;
+    p.block_tables += n * p.max_blocks;
+    p.seq_lens += n;
+    p.out += n * p.hq * D;
+    if (p.paged_nsplit > 1) {
+      const int64_t rows = n * p.paged_nsplit * p.hq;
+      p.part_o = static_cast<char*>(p.part_o) + rows * D * (KV == kKvF32 ? 4 : 2);
+      p.part_ml += rows * kPartMl;
+    }
+  }
+  return hipSuccess;
+}
+
 template <int D, int KV>
 static hipError_t launch_attn_t(const AttnParams& p, int grid, hipStream_t stream) {
-  // (More than 16 query heads per KV head: several row tiles.)
-  if (p.recs == nullptr && p.g <= kPagedRows)
-    hipLaunchKernelGGL((paged_kernel<D, KV>), dim3((static_cast<unsigned>(grid) + kXcds - 1) / kXcds * kXcds),
-                       dim3(64 * kPagedWaves), 0, stream, p);
-  else if (p.recs == nullptr)
-    hipLaunchKernelGGL((attn_kernel<D, KV, false, true>), dim3(grid), dim3(kThreads), 0, stream, p);
-  else if (p.two_windows)
+  if (p.recs == nullptr) return launch_paged_t<D, KV>(p, stream);
+  if (p.two_windows)
     hipLaunchKernelGGL((attn_kernel<D, KV, true, false>), dim3(grid), dim3(kThreads), 0, stream, p);
   else
     hipLaunchKernelGGL((attn_kernel<D, KV, false, false>), dim3(grid), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 
-hipError_t launch_merge(const MergeParams& p, int head_dim, int kv_kind, hipStream_t stream) {
-  const int rows = p.num_seqs * p.hq;
-  if (rows <= 0) return hipSuccess;
-  const bool f16 = kv_kind != kKvF32;
-  const int per = kMergeThreads / 64;
-  const dim3 grid((rows + per - 1) / per), block(kMergeThreads);
-  if (head_dim == 128) {
-    if (f16)
-      hipLaunchKernelGGL((merge_kernel<128, true>), grid, block, 0, stream, p);
-    else
-      hipLaunchKernelGGL((merge_kernel<128, false>), grid, block, 0, stream, p);
-  } else {
-    if (f16)
-      hipLaunchKernelGGL((merge_kernel<64, true>), grid, block, 0, stream, p);
-    else
-      hipLaunchKernelGGL((merge_kernel<64, false>), grid, block, 0, stream, p);
+template <int D, bool F16>
+static hipError_t launch_merge_t(MergeParams p, hipStream_t stream) {
+  constexpr int kPer = kMergeThreads / 64;  // rows per workgroup
+  // (Whole beams, and whole beams' virtual ones.)
+  const int64_t fit = kMaxLaunchThreads / kMergeThreads * kPer / p.hq / p.q_len * p.q_len;
+  const int64_t most = fit > p.q_len ? fit : p.q_len;
+  for (int64_t left = p.num_seqs; left > 0; left -= most) {
+    const int64_t n = left < most ? left : most;
+    p.num_seqs = static_cast<int32_t>(n);
+    const unsigned grid = static_cast<unsigned>((n * p.hq + kPer - 1) / kPer);
+    hipLaunchKernelGGL((merge_kernel<D, F16>), dim3(grid), dim3(kMergeThreads), 0, stream, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    p.seq_lens += n / p.q_len;
+    p.out += n * p.hq * D;
+    if (p.slot_tab) {
+      p.slot_tab += n * p.slot_stride;
+      p.build_len += n;
+    } else {
+      const int64_t rows = n * p.paged_nsplit * p.hq;
+      p.part_o = static_cast<const char*>(p.part_o) + rows * D * (F16 ? 2 : 4);
+      p.part_ml += rows * kPartMl;
+    }
   }
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+hipError_t launch_merge(const MergeParams& p, int head_dim, int kv_kind, hipStream_t stream) {
+  const bool f16 = kv_kind != kKvF32;
+  if (head_dim == 128) return f16 ? launch_merge_t<128, true>(p, stream) : launch_merge_t<128, false>(p, stream);
+  return f16 ? launch_merge_t<64, true>(p, stream) : launch_merge_t<64, false>(p, stream);
 }
 
 hipError_t launch_attn(const AttnParams& p, int grid, int head_dim, int kv_kind, hipStream_t stream) {
