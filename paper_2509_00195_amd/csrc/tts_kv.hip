@@ -264,19 +264,34 @@ __global__ __launch_bounds__(kKvThreads) void copy_kernel(CopyParams p) {
 
 }  // namespace
 
+// (A launch holds fewer than 2^32 threads: calls of more beams are made in
+// runs.)
+constexpr int kMaxAppendBeams = 0xFFFFFFFFu / kKvThreads / 2;
+
+template <int KV>
+static hipError_t launch_append_t(AppendParams p, int num_seqs, hipStream_t stream) {
+  const int64_t token = static_cast<int64_t>(p.hkv) * p.head_dim * (KV == 0 ? 4 : 2);
+  for (int left = num_seqs; left > 0; left -= kMaxAppendBeams) {
+    const int n = left < kMaxAppendBeams ? left : kMaxAppendBeams;
+    hipLaunchKernelGGL(append_kernel<KV>, dim3(2 * n), dim3(kKvThreads), 0, stream, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    p.k_new = static_cast<const char*>(p.k_new) + n * token;
+    p.v_new = static_cast<const char*>(p.v_new) + n * token;
+    p.block_tables += static_cast<int64_t>(n) * p.max_blocks;
+    p.seq_lens += n;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* block_tables, const int32_t* seq_lens,
                          void* k_cache, void* v_cache, float* k_scale, float* v_scale, int num_seqs, int max_blocks,
                          int num_blocks, int hkv, int head_dim, int kv_kind, hipStream_t stream) {
-  if (num_seqs <= 0) return hipSuccess;
-  AppendParams p{k_new, v_new, block_tables, seq_lens, k_cache, v_cache, k_scale, v_scale,
-                 max_blocks, num_blocks, hkv, head_dim};
-  if (kv_kind == 0)
-    hipLaunchKernelGGL(append_kernel<0>, dim3(2 * num_seqs), dim3(kKvThreads), 0, stream, p);
-  else if (kv_kind == 1)
-    hipLaunchKernelGGL(append_kernel<1>, dim3(2 * num_seqs), dim3(kKvThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL(append_kernel<2>, dim3(2 * num_seqs), dim3(kKvThreads), 0, stream, p);
-  return hipGetLastError();
+  const AppendParams p{k_new, v_new, block_tables, seq_lens, k_cache, v_cache, k_scale, v_scale,
+                       max_blocks, num_blocks, hkv, head_dim};
+  if (kv_kind == 0) return launch_append_t<0>(p, num_seqs, stream);
+  if (kv_kind == 1) return launch_append_t<1>(p, num_seqs, stream);
+  return launch_append_t<2>(p, num_seqs, stream);
 }
 
 hipError_t launch_copy_blocks(const int32_t* pairs, int num_pairs, void* k_cache, void* v_cache, float* k_scale,

@@ -1,8 +1,9 @@
-"""A paged call of more than 2^32 threads in both of its launches (48 GB): made in runs of whole beams.
+"""Calls of more than 2^32 threads, which no launch holds: made in runs of whole beams.
 
-17 query heads per KV head take several row tiles, 512 threads per workgroup, and two splits per beam, so the attention
-of 4,194,308 beams has 8,388,616 workgroups (8,388,607 fit a launch) and the merge 71 million rows (67 million fit).
-Nearly all beams are empty; those at the ends of the runs are not.
+The paged call (48 GB) is beyond one launch in both of its kernels: 17 query heads per KV head take several row tiles,
+512 threads per workgroup, and two splits per beam, so the attention of 4,194,308 beams has 8,388,616 workgroups
+(8,388,607 fit) and the merge 71 million rows (67 million fit). Nearly all beams are empty; those at the ends of the
+runs are not. The append has two workgroups of 256 threads per beam (8,388,607 beams fit).
 """
 
 import math
@@ -10,7 +11,7 @@ import math
 import pytest
 import torch
 
-from paper_2509_00195_amd import make_desc, tts_paged_decode_attn, tts_paged_decode_workspace_size
+from paper_2509_00195_amd import make_desc, tts_append_kv, tts_paged_decode_attn, tts_paged_decode_workspace_size
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +53,21 @@ def test_call_of_more_threads_than_a_launch_holds():
         assert int(torch.count_nonzero(out[at:at + (1 << 18)])) == 0, at
     del out, ws, q, tables
     torch.cuda.empty_cache()
+
+
+def test_append_of_more_beams_than_a_launch_holds():
+    run = (2 ** 32 - 1) // 512
+    n = run + 3
+    picks = torch.tensor([0, 1, run - 1, run, run + 1, n - 1], device="cuda")
+    lens = torch.zeros(n, dtype=torch.int32, device="cuda")
+    tables = torch.zeros((n, 1), dtype=torch.int32, device="cuda")
+    lens[picks] = 5
+    tables[picks, 0] = torch.arange(len(picks), dtype=torch.int32, device="cuda")
+    k_new, v_new = (torch.randn((n, 1, D), device="cuda").bfloat16() for _ in range(2))
+    k = torch.zeros((len(picks), 1, 16, D), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros((len(picks), 1, D, 16), dtype=torch.bfloat16, device="cuda")
+    tts_append_kv(make_desc(G, 1, D, 16, "bf16", "bf16"), n, k_new, v_new, tables, 1, lens, len(picks), k, v, None, None)
+    assert torch.equal(k[:, :, 4], k_new[picks]) and torch.equal(v[..., 4], v_new[picks])
+    k[:, :, 4] = 0
+    v[..., 4] = 0
+    assert int(torch.count_nonzero(k)) == int(torch.count_nonzero(v)) == 0
