@@ -1,7 +1,11 @@
 """The merge of partial states at the edges of its rounds: 64 slots per table round, 32 per element round.
 
-The paged call writes one state per split of 64 blocks of the length bound, so the bound sets the slot count; one
-beam fills every split, one leaves all but the first empty, one is empty.
+The paged call writes one state per split of 32 blocks of the length bound, so the bound sets the slot count; one beam
+fills every split, one leaves all but the first empty, one is empty, one leaves the last empty.
+
+Every split's state is exact: its scores are one integer in log2 units, its values one small integer per dimension, so
+probabilities (powers of two), sums and stored elements carry no rounding, and the result is off by that of the merge
+alone, in fp32. A dropped, repeated or exchanged slot moves it far more, which the test checks of every slot.
 """
 
 import math
@@ -14,36 +18,54 @@ from paper_2509_00195_amd import make_desc, tts_paged_decode_attn, tts_paged_dec
 
 pytestmark = pytest.mark.gpu
 
-POOL, G, HKV = 48, 3, 2
+G, HKV, SPLIT, VMAX = 3, 2, 512, 8
 
 
-@pytest.mark.parametrize("kv,d,tol", [("bf16", 128, 1e-2), ("bf16", 64, 1e-2), ("f32", 128, 1e-4), ("f32", 64, 1e-4)])
-@pytest.mark.parametrize("slots", [2, 31, 32, 33, 63, 64, 65, 97])
-def test_merge_slot_counts(kv, d, tol, slots):
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("slots", [2, 31, 32, 33, 63, 64, 65, 96, 97, 129])
+def test_merge_slot_counts(kv, d, slots):
     g = torch.Generator().manual_seed(slots)
     dt = torch.float32 if kv == "f32" else torch.bfloat16
-    bound = 1024 * slots
-    lens = np.array([bound, 7, 0, bound - 1024 - 5], np.int32)
-    tables = torch.randint(0, POOL, (len(lens), bound // 16), generator=g, dtype=torch.int32)
-    q = torch.randn((len(lens), G * HKV, d), generator=g).to(dt)
-    k = torch.randn((POOL, HKV, 16, d), generator=g).to(dt)
-    v = torch.randn((POOL, HKV, d, 16), generator=g).to(dt)
-    desc = make_desc(G * HKV, HKV, d, 16, kv, kv)
+    bound = SPLIT * slots
+    # A stored element is (tokens x value) / 2^e in fp16, exact while that product has 11 bits: 512 v, 7 v, 8 x 63 v.
+    lens = np.array([bound, 7, 0, bound - SPLIT - 8], np.int32)
+    order = torch.randperm(slots, generator=g)  # split j: 32 times block order[j]
+    tables = order.to(torch.int32).repeat_interleave(SPLIT // 16).expand(len(lens), -1).contiguous()
+    score = torch.randint(-3, 4, (slots, HKV), generator=g)
+    value = torch.randint(-VMAX, VMAX + 1, (slots, HKV, d), generator=g)
+    k = torch.zeros((slots, HKV, 16, d), dtype=dt)
+    k[order, :, :, 0] = score[:, :, None].to(dt)
+    v = torch.zeros((slots, HKV, d, 16), dtype=dt)
+    v[order] = value[..., None].to(dt)
+    sign = torch.tensor([1, -1, 0]).repeat(HKV)  # heads with weights 2^score, 2^-score and 1
+    q = torch.zeros((len(lens), G * HKV, d), dtype=dt)
+    q[:, :, 0] = sign.to(dt)
+    desc = make_desc(G * HKV, HKV, d, 16, kv, kv, "f32", math.log(2.0))
     nbytes = tts_paged_decode_workspace_size(desc, len(lens), bound)
-    assert nbytes > 0
+    rows = len(lens) * slots * G * HKV
+    assert nbytes == sum(-(-rows * n // 256) * 256 for n in (d * (4 if kv == "f32" else 2), 16))
     out = torch.full((len(lens), G * HKV, d), float("nan"), device="cuda")
     ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")  # every float a NaN
     dev = [t.cuda() for t in (q, k, v, tables, torch.from_numpy(lens))]
     tts_paged_decode_attn(desc, len(lens), dev[0], dev[1], dev[2], None, None, dev[3], tables.shape[1], dev[4], bound,
-                          POOL, out, ws, nbytes)
+                          slots, out, ws, nbytes)
     got = out.cpu().double()
+    # slots + 8 roundings of sums and products, each at most 2^-23 of the largest value
+    tol = (slots + 8) * 2.0 ** -23 * VMAX
+    kvh = torch.arange(G * HKV) // G
+    val = value[:, kvh].double()  # [slots][heads][d]
     for b, n in enumerate(lens):
         if n == 0:
             assert torch.all(got[b] == 0)
             continue
-        ids = tables[b, : -(-int(n) // 16)].long()
-        kk = k[ids].double().permute(1, 0, 2, 3).reshape(HKV, -1, d)[:, :n]
-        vv = v[ids].double().permute(1, 0, 3, 2).reshape(HKV, -1, d)[:, :n]
-        s = torch.matmul(q[b].double().reshape(HKV, G, d), kk.transpose(1, 2)) / math.sqrt(d)
-        ref = torch.matmul(torch.softmax(s, -1), vv).reshape(G * HKV, d)
+        tokens = (int(n) - SPLIT * torch.arange(slots)).clamp(0, SPLIT).double()
+        w = tokens[:, None] * 2.0 ** (score[:, kvh] * sign)
+        total, den = (w[..., None] * val).sum(0), w.sum(0)[:, None]
+        ref = total / den
         assert float((got[b] - ref).abs().max()) <= tol, (b, int(n))
+        used = int((tokens > 0).sum())
+        for j in range(used if used > 1 else 0):
+            for times in (-1, 1):  # without slot j, and with it twice
+                moved = (total + times * w[j][:, None] * val[j]) / (den + times * w[j][:, None])
+                assert float((moved - ref).abs().max()) > 20 * tol, (b, j)
