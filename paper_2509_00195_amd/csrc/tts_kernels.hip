@@ -151,54 +151,44 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // a row call together.
 //
 // partial_exp: the exponent e with every |o| / 2^e below 1, reduced across
-// the row's lanes (every lane of the wave must call it).
-template <int D, int KV>
+// the row's lanes (every lane of the wave must call it). This and
+// store_partial serve wide units, which fp32 caches do not have.
+template <int D>
 __device__ __forceinline__ int partial_exp(const f32x4 (&o)[D / 16]) {
-  int e = 0;
-  if constexpr (KV != kKvF32) {
-    float amax = 0.f;
+  float amax = 0.f;
 #pragma unroll
-    for (int t = 0; t < D / 16; ++t)
+  for (int t = 0; t < D / 16; ++t)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) amax = fmaxf(amax, __builtin_fabsf(o[t][j]));
-    amax = fmaxf(amax, __shfl_xor(amax, 16));
-    amax = fmaxf(amax, __shfl_xor(amax, 32));
-    // amax = f 2^e with f in [0.5, 1): every element over 2^e is in [-1, 1].
-    if (amax > 0.f && amax <= 3.0e38f) e = __builtin_amdgcn_frexp_expf(amax);
-  }
-  return e;
+    for (int j = 0; j < 4; ++j) amax = fmaxf(amax, __builtin_fabsf(o[t][j]));
+  amax = fmaxf(amax, __shfl_xor(amax, 16));
+  amax = fmaxf(amax, __shfl_xor(amax, 32));
+  // amax = f 2^e with f in [0.5, 1): every element over 2^e is in [-1, 1].
+  return (amax > 0.f && amax <= 3.0e38f) ? __builtin_amdgcn_frexp_expf(amax) : 0;
 }
 
 // store_partial: the row's stores, with inv = 1 / l (0 for l = 0) and e
 // from above. (Scaling by 2^-e alone, not by 1 / l as well, takes one
 // instruction per element instead of two.)
-template <int D, int KV>
+template <int D>
 __device__ __forceinline__ void store_partial(void* part_o, float* part_ml, int64_t prow, const f32x4 (&o)[D / 16],
                                               float m, float l, float inv, int e, int lq) {
-  float z = 1.f;
-  if constexpr (KV != kKvF32) {
-    uint32_t w[D / 8];
+  uint32_t w[D / 8];
 #pragma unroll
-    for (int t = 0; t < D / 16; ++t)
+  for (int t = 0; t < D / 16; ++t)
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        const f16x2 h = {static_cast<_Float16>(__builtin_ldexpf(o[t][j], -e)),
-                         static_cast<_Float16>(__builtin_ldexpf(o[t][j + 1], -e))};
-        w[2 * t + j / 2] = __builtin_bit_cast(uint32_t, h);
-      }
-    uint4* dst = reinterpret_cast<uint4*>(static_cast<uint16_t*>(part_o) + prow * D + (D / 4) * lq);
+    for (int j = 0; j < 4; j += 2) {
+      const f16x2 h = {static_cast<_Float16>(__builtin_ldexpf(o[t][j], -e)),
+                       static_cast<_Float16>(__builtin_ldexpf(o[t][j + 1], -e))};
+      w[2 * t + j / 2] = __builtin_bit_cast(uint32_t, h);
+    }
+  uint4* dst = reinterpret_cast<uint4*>(static_cast<uint16_t*>(part_o) + prow * D + (D / 4) * lq);
 #pragma unroll
-    for (int c = 0; c < D / 32; ++c) dst[c] = uint4{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]};
-    z = __builtin_ldexpf(inv, e);
-  } else {
-    f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(part_o) + prow * D + (D / 4) * lq);
-#pragma unroll
-    for (int t = 0; t < D / 16; ++t) dst[t] = o[t] * inv;
-  }
+  for (int c = 0; c < D / 32; ++c) dst[c] = uint4{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]};
   // A state without tokens (l = 0) takes no part in the merge's maximum; a
   // NaN m (a bad row) is kept.
   const float m_out = (l > 0.f || m != m) ? m : kNegInf;
-  if (lq == 0) *reinterpret_cast<f32x4*>(part_ml + prow * kPartMl) = f32x4{m_out, l, z, 0.f};
+  if (lq == 0)
+    *reinterpret_cast<f32x4*>(part_ml + prow * kPartMl) = f32x4{m_out, l, __builtin_ldexpf(inv, e), 0.f};
 }
 
 // Largest value over the sixteen lanes of a DPP row (rotations within it).
@@ -471,7 +461,6 @@ struct PairInfo {
   float vs0, vs1;  // value scale (fp8) or 1
 };
 
-// One pair against one row tile `r`.
 // Query operands of one row tile (lane: row 16r + ln, dims as K's).
 template <int D, int KV>
 struct QFrag {
@@ -959,7 +948,7 @@ __device__ __forceinline__ void issue_live(const AttnParams& p, const UnitRegs& 
 }
 
 // The unit's query rows, fetched into registers (thread t holds 16-byte
-// chunks t, t + 256, ... of the rows) while the previous unit finishes, then
+// chunks t, t + 512, ... of the rows) while the previous unit finishes, then
 // stored to LDS in the swizzled layout. Rows past nrows repeat row 0 (their
 // scores are always masked).
 // (A vector value rather than an array, so that it stays in registers.)
@@ -1046,7 +1035,6 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
   coords();
   const size_t blk_stride = static_cast<size_t>(p.hkv) * G::blk_bytes;
   constexpr bool paged = kPaged;
-  const float sc_w = p.scale_log2;
   const float sc = p.scale_log2;
   auto comb_slot = [&](int w, int i) { return comb + (w * kNt + i) * G::comb_floats; };  // (wave, its tile)
 
@@ -1062,7 +1050,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
     u = load_unit(p.recs, rec_idx, lane);
   } else {
     // Paged path: unit = (beam, KV head, split) from the workgroup id, one
-    // beam's g rows against up to 64 of its blocks.
+    // beam's g rows against up to 32 of its blocks.
     rec_idx = 0;
     paged_split = blockIdx.x % p.paged_nsplit;
     const int bh = blockIdx.x / p.paged_nsplit;
@@ -1250,13 +1238,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
                   pi.v1 = 2 * pp + 1 < nst ? kTok : 0;
                   pi.a0 = pi.a1 = 0;
                   pi.e0 = pi.e1 = nrows;
-                  pi.ks0 = pi.ks1 = sc_w;
+                  pi.ks0 = pi.ks1 = sc;
                   pi.vs0 = pi.vs1 = 1.f;
                   if constexpr (KV == kKvFp8) {
                     const float ks = e0 < kMaxEntries ? ksl : ksl2, vs = e0 < kMaxEntries ? vsl : vsl2;
                     const int i0 = e0 & (kMaxEntries - 1), i1 = e1 & (kMaxEntries - 1);
-                    pi.ks0 = sc_w * rlf(ks, i0);
-                    pi.ks1 = sc_w * rlf(ks, i1);
+                    pi.ks0 = sc * rlf(ks, i0);
+                    pi.ks1 = sc * rlf(ks, i1);
                     pi.vs0 = rlf(vs, i0);
                     pi.vs1 = rlf(vs, i1);
                   }
@@ -1361,13 +1349,13 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
 #pragma unroll
         for (int i = 0; i < kWideTiles; ++i) inv_[i] = lw_[i] > 0.f ? 1.f / lw_[i] : 0.f;
 #pragma unroll
-        for (int i = 0; i < kWideTiles; ++i) e_[i] = partial_exp<D, KV>(st[i].o);
+        for (int i = 0; i < kWideTiles; ++i) e_[i] = partial_exp<D>(st[i].o);
 #pragma unroll
         for (int i = 0; i < kWideTiles; ++i) {
           if (i >= wtiles || (halves && i != half)) continue;  // wave-uniform
           const int row = 16 * (tile0 + tstep * i) + ln;
           const int64_t prow = static_cast<int64_t>(kvh) * p.rows_per_head + prow0 + row;
-          if (row < nrows) store_partial<D, KV>(p.part_o, p.part_ml, prow, st[i].o, st[i].m, lw_[i], inv_[i], e_[i], lq);
+          if (row < nrows) store_partial<D>(p.part_o, p.part_ml, prow, st[i].o, st[i].m, lw_[i], inv_[i], e_[i], lq);
         }
         TTS_PROF_MARK(2, rec_idx);
         const int nu_rows_w = rfl(nu.nrows);
@@ -1389,7 +1377,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
       if (!fa_ready) issue_live(p, u, lane, &ext_len, &ext_build);
     } else {
       const int L = p.seq_lens[paged_b];
-      // Split j covers blocks [j * per, (j + 1) * per) of the beam (per <= 64).
+      // Split j covers blocks [j * per, (j + 1) * per) of the beam (per <= 32).
       const int per = (p.paged_max_len + kTok * p.paged_nsplit - 1) / (kTok * p.paged_nsplit);
       const int j = paged_split * per + lane;
       int nb = (L + kTok - 1) / kTok;
@@ -1703,7 +1691,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_kernel(AttnParams p) {
 }
 
 // ---- the paged path, up to 16 query heads per KV head ------------------------
-// One workgroup of four waves per (split of up to 64 blocks, KV head, beam):
+// One workgroup of four waves per (split of up to 32 blocks, KV head, beam):
 // one row tile, query rows held in registers, each wave streaming its share
 // of the pairs. Three workgroups share a compute unit (at most 168 registers
 // and 36 KB of LDS each), so that one's round trips to the length, the table
@@ -1731,7 +1719,7 @@ __global__ __launch_bounds__(64 * kPagedWaves, KV == kKvF32 && D == 128 ? 2 : 3)
   const size_t blk_stride = static_cast<size_t>(p.hkv) * G::blk_bytes;
   const unsigned char* kbase = static_cast<const unsigned char*>(p.k_cache) + kvh * G::blk_bytes;
   const unsigned char* vbase = static_cast<const unsigned char*>(p.v_cache) + kvh * G::blk_bytes;
-  // Split j covers blocks [j * per, (j + 1) * per) of the beam (per <= 64).
+  // Split j covers blocks [j * per, (j + 1) * per) of the beam (per <= 32).
   const int per = (p.paged_max_len + kTok * p.paged_nsplit - 1) / (kTok * p.paged_nsplit);
   const int j = split * per + lane;
   // Length and query rows together; the table only up to the length.

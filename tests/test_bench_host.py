@@ -36,7 +36,7 @@ def _counter_csv(path, counter, attn_kib, copy_kib):
             w.writerow({"Dispatch_Id": d, "Kernel_Name": "void tts::attn_kernel<128, 1, false>(tts::AttnParams)",
                         "Grid_Size": 65536, "Counter_Name": counter, "Counter_Value": v})
             d += 1  # the merge, not counted
-            w.writerow({"Dispatch_Id": d, "Kernel_Name": "void tts::merge_row_kernel<128, true>(tts::MergeParams)",
+            w.writerow({"Dispatch_Id": d, "Kernel_Name": "void tts::merge_kernel<128, true>(tts::MergeParams)",
                         "Grid_Size": 114688, "Counter_Name": counter, "Counter_Value": 999.0})
         for v in copy_kib:
             d += 1

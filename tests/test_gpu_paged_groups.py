@@ -12,7 +12,8 @@ from paper_2509_00195_amd import make_desc, tts_paged_decode_attn, tts_paged_dec
 pytestmark = pytest.mark.gpu
 
 POOL, HKV = 40, 3
-LENS = (1, 16, 17, 32, 33, 128, 129, 0, 700, 1023, 1024, 1025, 1100)
+# A split takes 512 tokens at the bounds 1024 and 2500 and 368 at 1100.
+LENS = (1, 16, 17, 32, 33, 128, 129, 0, 367, 368, 369, 511, 512, 513, 700, 1023, 1024, 1025, 1100)
 
 
 def tolerance(kv, v):

@@ -7,8 +7,8 @@ loop has no barrier); wide units (block pairs staged in LDS, a loop with
 barriers) decide for the whole workgroup. These inputs reach every case:
 
 (a) queries of two beams scaled x35 in the 7B 64-beam batch: only the row
-    tiles of those beams leave the window, so in a wide unit only one or two
-    of the four waves need the repeat and the others must take it with them;
+    tiles of those beams leave the window, so in a wide unit only some of the
+    eight waves need the repeat and the others must take it with them;
 (b) the same on a 1.5B-shaped batch of 8 beams whose plan has narrow units
     only, and through the paged call;
 (c) every score far below the window: keys 2 + N(0, 0.25), queries
@@ -17,7 +17,9 @@ barriers) decide for the whole workgroup. These inputs reach every case:
     scale 0.22 about -81;
 (d) only the prompt's keys shifted (scores about +185 in log2 units there,
     ordinary elsewhere): the row's partial states then carry references
-    hundreds apart and the merge must weigh the tail's states to zero.
+    hundreds apart and the merge must weigh the tail's states to zero;
+(e) wide units of up to eight row tiles, whose halves exchange tiles after
+    the repeat, with every number of pairs left for the last step.
 
 Tolerances are the parity ones (max abs 1e-2 for bf16 KV).
 """

@@ -123,10 +123,9 @@ def unit_rows(name, wide, nbins=256):
 
 
 def test_row_caps_are_chosen_per_batch():
-    """The planner models a batch with wide units of up to 192 rows (three row tiles per wave) and of up to 128
-    (two), and a batch that fits the workgroups with narrow units of up to 64 rows and of up to 42, and keeps
-    the cheaper plan: 192 / 64 for the 7B 64-beam tree, 128-row wide units for the balanced tree, 42-row
-    narrow units for the 1.5B 16-beam tree."""
+    """A batch of much KV per workgroup takes wide units of up to 128 rows (one row tile per wave) and narrow ones of
+    up to 32, others of up to 192 (two tiles) and 64, or 256-row wide units where these model faster: 192 / 64 for
+    the 7B 64-beam tree, 128 for the balanced tree; the 1.5B 16-beam tree's narrow units stay within 42 rows."""
     r = unit_rows("7b64", wide=True)
     assert r and 128 < max(r) <= 192
     assert 42 < max(unit_rows("7b64", wide=False)) <= 64
