@@ -189,7 +189,7 @@ def meta_timings(wl, desc, prev, reps=5):
 
 
 COPY_KERNEL = "bitwise_not"  # the calibration copy: dst = ~src, one read and one write per byte
-ATTN_KERNEL = "attn_kernel"
+ATTN_KERNEL = {"prefix": "attn_kernel", "paged": "paged_kernel"}  # (paged: up to 16 query heads per KV head)
 
 
 def _counter_rows(path, counter):
@@ -208,6 +208,7 @@ def ingest_traffic(args):
     if args.copy_mib <= 0:
         raise SystemExit("--ingest-traffic needs the --copy-mib the counter runs used")
     copy_kib = args.copy_mib * 1024.0
+    kernel = ATTN_KERNEL[args.variant]
     rec = {"kernel_sha": kernel_sha(), "entries": {}}
     if os.path.exists(TRAFFIC_FILE):
         with open(TRAFFIC_FILE) as f:
@@ -218,11 +219,11 @@ def ingest_traffic(args):
     total = 0.0
     for path, counter in zip(args.ingest_traffic, ("FETCH_SIZE", "WRITE_SIZE")):
         rows = _counter_rows(path, counter)
-        attn = [float(r["Counter_Value"]) for r in rows if ATTN_KERNEL in r["Kernel_Name"]]
+        attn = [float(r["Counter_Value"]) for r in rows if kernel in r["Kernel_Name"]]
         copy = [float(r["Counter_Value"]) for r in rows if COPY_KERNEL in r["Kernel_Name"]
                 and int(r["Grid_Size"]) > 0]
         if not attn or not copy:
-            raise SystemExit(f"{path}: no {ATTN_KERNEL} or {COPY_KERNEL} dispatches with {counter}")
+            raise SystemExit(f"{path}: no {kernel} or {COPY_KERNEL} dispatches with {counter}")
         copy_kib_meas = copy[-1]  # the last copy dispatches are the calibration copies
         factor = copy_kib / copy_kib_meas
         kib = float(np.mean(attn))
@@ -482,7 +483,7 @@ def main():
         "roofline": {
             "bound": "hbm",
             "kernel": "attn_kernel (work units of tts_prefix_decode_partials)" if args.variant == "prefix"
-                      else "attn_kernel + merge_kernel (tts_paged_decode_attn)",
+                      else "paged_kernel + merge_kernel (tts_paged_decode_attn)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

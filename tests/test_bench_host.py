@@ -26,14 +26,14 @@ def test_more_than_one_gpu_is_refused():
     assert "one GPU" in r.stderr and r.stdout == ""
 
 
-def _counter_csv(path, counter, attn_kib, copy_kib):
+def _counter_csv(path, counter, attn_kib, copy_kib, kernel="attn_kernel<128, 1, false, false>"):
     with open(path, "w", newline="") as f:
         w = csv.DictWriter(f, fieldnames=["Dispatch_Id", "Kernel_Name", "Grid_Size", "Counter_Name", "Counter_Value"])
         w.writeheader()
         d = 0
         for v in attn_kib:
             d += 1
-            w.writerow({"Dispatch_Id": d, "Kernel_Name": "void tts::attn_kernel<128, 1, false>(tts::AttnParams)",
+            w.writerow({"Dispatch_Id": d, "Kernel_Name": f"void tts::{kernel}(tts::AttnParams)",
                         "Grid_Size": 65536, "Counter_Name": counter, "Counter_Value": v})
             d += 1  # the merge, not counted
             w.writerow({"Dispatch_Id": d, "Kernel_Name": "void tts::merge_kernel<128, true>(tts::MergeParams)",
@@ -42,6 +42,21 @@ def _counter_csv(path, counter, attn_kib, copy_kib):
             d += 1
             w.writerow({"Dispatch_Id": d, "Kernel_Name": "void at::native::bitwise_not_kernel(...)",
                         "Grid_Size": 268435456, "Counter_Name": counter, "Counter_Value": v})
+
+
+def test_traffic_record_of_the_paged_path(tmp_path, monkeypatch):
+    """The paged path's kernel is counted, not the prefix path's."""
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tmp_path / "traffic.json"))
+    files = [tmp_path / "fetch.csv", tmp_path / "write.csv"]
+    for f, counter in zip(files, ("FETCH_SIZE", "WRITE_SIZE")):
+        _counter_csv(f, counter, [1000.0], [262144.0], kernel="paged_kernel<128, 1>")
+    args = argparse.Namespace(copy_mib=256, ingest_traffic=[str(f) for f in files], config="7b64", variant="prefix")
+    with pytest.raises(SystemExit):
+        bench.ingest_traffic(args)
+    args.variant = "paged"
+    bench.ingest_traffic(args)
+    ent = json.load(open(tmp_path / "traffic.json"))["entries"]["7b64:paged"]
+    assert ent["bytes_per_launch"] == pytest.approx(2000 * 1024.0)
 
 
 def test_traffic_record_scales_by_the_copy(tmp_path, monkeypatch):
