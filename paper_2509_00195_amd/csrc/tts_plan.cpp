@@ -48,20 +48,28 @@ namespace {
 //   pair): 5.3 us + (0.27 + 0.011 tiles) us per 8 KiB block; more tiles:
 //   5.3 us + (0.12 + 0.029 tiles) us. fp8: 5.3 us + (0.175 + 0.0325 tiles)
 //   us per block, in both forms.
-// fp32 caches scale the block terms by their bytes and every shape the tile
-// term by the head size.
+// * fp32 (16 rows to a wave group, four groups of two waves above 32 rows):
+//   the larger of 0.26 us per 8 KiB of blocks and of the matrix cores' time,
+//   0.24 us per block and row tile (D 128; four times the largest tile's
+//   blocks with four groups, whose waves do not help each other out); 1.5 us
+//   more with several groups. Fitted to whole calls: 36 drawn decode and
+//   verification batches of both head sizes take 0.945 times as long as with
+//   the bf16 terms scaled by the bytes, 40 of D 64 0.940 times.
+// Every shape scales the tile term by the head size.
 constexpr double kNarrowFixedUs = 3.0, kNarrowBlockUs = 0.26, kRowUs = 0.05, kGroupsUs = 1.5;
 constexpr double kWideFixedUs = 5.3;
 constexpr double kHalvesBlockUs = 0.27, kHalvesTileUs = 0.011;
 constexpr double kFullBlockUs = 0.12, kFullTileUs = 0.029;
 constexpr double kFp8NarrowBlockUs = 0.225;
 constexpr double kFp8WideBlockUs = 0.175, kFp8WideTileUs = 0.0325;
+constexpr double kF32NarrowBlockUs = 0.26, kF32TileBlockUs = 0.24;
 // Where the batch holds many bytes per workgroup the narrow units' blocks
 // come at the rate of the memory, not of one workgroup's round trips: 0.33
 // us per block with every workgroup streaming (straggler batch) against 0.26
 // where half of them run wide units (64-beam tree). Above this many KV bytes
 // per workgroup the bf16 narrow block term is scaled by 1.3.
 constexpr double kStreamBytesPerGroup = 400e3, kStreamScale = 1.3;
+constexpr int kGroupRows = 32;  // rows of a narrow unit whose waves work in one group
 constexpr int kXcds = 8;  // workgroup k of a launch runs on XCD k % 8
 constexpr int kFewWideRows = 192, kStreamWideRows = 128;  // wide-unit row caps tried besides kMaxWideRows
 constexpr double kCapGain = 0.97;
@@ -70,22 +78,41 @@ constexpr double kCapGain = 0.97;
 constexpr double kMergeFixedUs = 3.2;
 constexpr double kMergeSlotUs = 0.06;
 
-constexpr int kGroupRows = 32;  // rows of a narrow unit whose waves work in one group
-
 int tiles_of(int rows) { return (rows + 15) / 16; }
+
+// The blocks of a narrow unit: how many, how many with rows of both wave
+// groups, which both read, and how many of each row tile.
+struct NarrowLoad {
+  int blocks = 0, span = 0;
+  int tile[kMaxRows / 16] = {};
+  // n blocks of the unit's rows [r0, r1).
+  NarrowLoad& add(int n, int r0, int r1) {
+    blocks += n;
+    if (r0 < kGroupRows && r1 > kGroupRows) span += n;
+    for (int t = r0 / 16; 16 * t < r1; ++t) tile[t] += n;
+    return *this;
+  }
+};
 
 struct CostModel {
   double blk_bytes, q_row_bytes, part_row_bytes, d_scale;
-  bool fp8 = false;
+  bool fp8 = false, f32 = false;
   double narrow_scale = 1.0;  // kStreamScale where the batch is bound by streaming
   double row_us() const { return kRowUs * (q_row_bytes + part_row_bytes) / 800.0; }
   // Narrow units: the waves split the block pairs, every wave runs every tile.
-  // span: the blocks with rows of both wave groups, which both read.
-  double narrow_us(int blocks, int span, int rows) const {
-    return kNarrowFixedUs + (rows > kGroupRows ? kGroupsUs : 0.0) + (blocks + span) * narrow_block_us() +
+  double narrow_us(const NarrowLoad& x, int rows) const {
+    if (f32) {
+      const int most = std::max(std::max(x.tile[0], x.tile[1]), std::max(x.tile[2], x.tile[3]));
+      const int tiles = rows > 32 ? 4 * most : x.tile[0] + x.tile[1];
+      return kNarrowFixedUs + (rows > 16 ? kGroupsUs : 0.0) +
+             std::max(x.blocks * narrow_block_us(), tiles * f32_tile_us()) + rows * row_us();
+    }
+    return kNarrowFixedUs + (rows > kGroupRows ? kGroupsUs : 0.0) + (x.blocks + x.span) * narrow_block_us() +
            rows * row_us();
   }
+  double f32_tile_us() const { return kF32TileBlockUs * d_scale; }
   double narrow_block_us() const {
+    if (f32) return blk_bytes * (kF32NarrowBlockUs / 8192);
     return fp8 ? kFp8NarrowBlockUs : narrow_scale * blk_bytes * (kNarrowBlockUs / 8192);
   }
   // Wide units: one block, all tiles.
@@ -149,12 +176,13 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // Beams per narrow unit: set per candidate row cap below.
   auto narrow_beams = [&](int32_t cap_rows) { return std::max(1, std::min(kMaxUnitBeams, cap_rows / g)); };
   int32_t RB = narrow_beams(kMaxRows);
-  // Beams per wide unit (bf16 and fp8 caches; fp32 caches use narrow-sized
-  // chunks): set per candidate row cap below.
+  // Beams per wide unit (bf16 and fp8 caches; segments of fp32 caches are cut
+  // into chunks of as many rows as a narrow unit holds, whatever the cap of
+  // the narrow list): set per candidate row cap below.
   const bool wide_mode = shape.kv_bytes <= 2;
   int32_t RW = RB;
   auto wide_beams = [&](int32_t cap_rows) {
-    return wide_mode ? std::max(1, std::min(kMaxWideBeams, cap_rows / g)) : RB;
+    return wide_mode ? std::max(1, std::min(kMaxWideBeams, cap_rows / g)) : narrow_beams(kMaxRows);
   };
   const int32_t nseg = static_cast<int32_t>(m.seg_req.size());
   const int32_t nbins = std::max(1, shape.num_bins);
@@ -168,6 +196,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   cm.part_row_bytes = 2.0 * (shape.head_dim * (shape.kv_bytes == 4 ? 4.0 : 2.0) + 4 * kPartMl);
   cm.d_scale = shape.head_dim / 128.0;
   cm.fp8 = shape.kv_bytes == 1;
+  cm.f32 = shape.kv_bytes == 4;
 
   const bool streaming = static_cast<double>(m.unique_blocks) * hkv * cm.blk_bytes > kStreamBytesPerGroup * nbins;
   if (streaming) cm.narrow_scale = kStreamScale;
@@ -256,7 +285,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // least share of the modelled time, its units' time over the workgroups
   // plus the merge of its pieces' states (else the fastest). The narrow list
   // is cut greedily into units that fit T.
-  auto span_of = [&](int32_t blocks, int32_t rows) { return rows > kGroupRows ? blocks : 0; };
+  auto narrow_us = [&](int32_t blocks, int32_t rows) { return cm.narrow_us(NarrowLoad().add(blocks, 0, rows), rows); };
   auto make_templates = [&](double T, std::vector<Tmpl>& tm) {
     tm.clear();
     int32_t ngroups = 0;
@@ -271,13 +300,13 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       bool have = false, best_fits = false;
       for (int32_t mode : {kModeWide, kModeNarrow}) {
         if (mode == kModeWide && !wide_mode) continue;
-        const int32_t cap = mode == kModeWide ? RW : RB;
+        const int32_t cap = mode == kModeWide || !wide_mode ? RW : RB;
         for (int32_t C = (G + cap - 1) / cap; C <= std::min(G, 4 * ((G + cap - 1) / cap)); ++C) {
           const int32_t rows = ((G + C - 1) / C) * g;
           const int32_t max_ent = mode == kModeWide ? kMaxUnitEntries : kMaxEntries;
           for (int32_t P = std::max(1, (n + max_ent - 1) / max_ent); P <= np; ++P) {
             const int32_t blocks = std::min(n, 2 * ((np + P - 1) / P));
-            const double us = mode == kModeWide ? cm.wide_us(blocks, rows) : cm.narrow_us(blocks, span_of(blocks, rows), rows);
+            const double us = mode == kModeWide ? cm.wide_us(blocks, rows) : narrow_us(blocks, rows);
             const double share = C * P * us * hkv / nbins + kMergeSlotUs * P;
             const bool fits = us <= T;
             const bool better = !have || (fits && !best_fits) ||
@@ -304,7 +333,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
           t.seg = s;
           t.a = a;
           t.b = e;
-          t.cost = t.mode == kModeWide ? cm.wide_us(e - a, rows) : cm.narrow_us(e - a, span_of(e - a, rows), rows);
+          t.cost = t.mode == kModeWide ? cm.wide_us(e - a, rows) : narrow_us(e - a, rows);
           t.group = ngroups;
           tm.push_back(t);
         }
@@ -312,26 +341,27 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       }
     }
     Tmpl cur;
-    // The open unit: its static items, those with rows of both wave groups,
-    // and the LIVE and extension items.
-    int32_t nblk = 0, nspan = 0, nlive_ext = 0;
-    auto spans = [&](const NItem& it, int32_t lo) {
-      return (it.flags & kEntExt) == 0 && (it.p0 - lo) * g < kGroupRows && (it.p1 - lo) * g > kGroupRows;
+    // The open unit's static items, and its LIVE and extension items.
+    NarrowLoad load;
+    int32_t nlive_ext = 0;
+    auto with = [&](NarrowLoad x, const NItem& it, int32_t lo) {
+      return (it.flags & kEntExt) ? x : x.add(1, (it.p0 - lo) * g, (it.p1 - lo) * g);
     };
     auto flush = [&]() {
       if (cur.b == cur.a) return;
-      cur.cost = cm.narrow_us(nblk, nspan, (cur.hi - cur.lo) * g);
+      cur.cost = cm.narrow_us(load, (cur.hi - cur.lo) * g);
       tm.push_back(cur);
       cur.a = cur.b;
-      nblk = nspan = nlive_ext = 0;
+      load = NarrowLoad();
+      nlive_ext = 0;
     };
     for (int32_t k = 0; k < static_cast<int32_t>(items.size()); ++k) {
       const NItem& it = items[k];
-      const int32_t blk = (it.flags & kEntExt) ? 0 : 1, live = (it.flags & (kEntLive | kEntExt)) ? 1 : 0;
+      const int32_t live = (it.flags & (kEntLive | kEntExt)) ? 1 : 0;
       if (cur.b > cur.a) {
         const int32_t lo = std::min(cur.lo, it.p0), hi = std::max(cur.hi, it.p1);
         const bool fits = hi - lo <= RB && cur.b - cur.a + 1 <= kMaxUnitEntries && nlive_ext + live <= kMaxEntries &&
-                          cm.narrow_us(nblk + blk, nspan + (spans(it, lo) ? 1 : 0), (hi - lo) * g) <= T;
+                          cm.narrow_us(with(load, it, lo), (hi - lo) * g) <= T;
         if (!fits) flush();
       }
       if (cur.b == cur.a) {
@@ -341,8 +371,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       cur.lo = std::min(cur.lo, it.p0);
       cur.hi = std::max(cur.hi, it.p1);
       cur.b = k + 1;
-      nblk += blk;
-      nspan += spans(it, cur.lo) ? 1 : 0;
+      load = with(load, it, cur.lo);
       nlive_ext += live;
     }
     flush();
@@ -501,7 +530,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     for (const NItem& it : items)
       if (!(it.flags & kEntExt)) work += cm.narrow_block_us();
     for (int32_t s = 0; s < nseg; ++s)
-      if (wide[s]) work += m.seg_nblocks[s] * cm.wide_block_us(RW * g);
+      if (wide[s])
+        work += m.seg_nblocks[s] * (cm.f32 ? tiles_of((m.seg_beam_end[s] - m.seg_beam_begin[s]) * g) * cm.f32_tile_us()
+                                           : cm.wide_block_us(RW * g));
     work = work * hkv / nbins;
     P.work_us = work;
     P.chained = false;
@@ -564,6 +595,11 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // * Other batches take narrow units of up to 64 rows (7B 64-beam tree 23.1
   //   us per call against 24.2 with 32) and wide units of up to 192 rows, or
   //   256.
+  // * fp32 caches try 64, 32 and 16 rows: streaming tails are fastest in one
+  //   or two wave groups (28 heads of 4, 4 requests of 5 beams of 8k tokens:
+  //   125 us per call against 166 to 176 with 64 rows), heavy segments in
+  //   units of 64 rows (verification of three tokens, 2 x 24 beams: 429
+  //   against 535 with 32).
   // A warm re-plan keeps the earlier plan's caps.
   // Smaller units write more partial states. The call that keeps them in the
   // library's scratch array refuses a plan that outgrows it, so a plan that
@@ -595,7 +631,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   if (!warm) {
     P.few_states = false;
     P.few_ratio = 0;
-    set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming ? kGroupRows : kMaxRows);
+    set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming && wide_mode ? kGroupRows : kMaxRows);
     double best = search();
     // Runs the search at other caps and keeps its plan if keep (of its
     // modelled time) says so, else restores the plan at hand.
@@ -626,6 +662,8 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       if (wide[s] && (G + RW - 1) / RW != (G + most - 1) / most) chunks_differ = true;
     }
     if (chunks_differ) try_caps(kMaxWideRows, P.narrow_rows, [&](double us) { return us < kCapGain * best; });
+    for (int32_t rows : {kGroupRows, kGroupRows / 2})
+      if (cm.f32) try_caps(P.wide_rows, rows, [&](double us) { return us < kCapGain * best; });
     if (over(tm)) {
       const double rows = rows_of(tm);
       P.few_states = true;

@@ -165,3 +165,29 @@ def test_states_fit_the_scratch_array():
     own = rows[rows[:, 2] == 0]
     states = len(np.unique(own[:, 0].astype(np.int64) * len(lens) + own[:, 3]))
     assert states * g * hkv * (2 * d + 16) <= 64 << 20
+
+
+@pytest.mark.parametrize("name", ["1p5b16", "7b64", "7b64_balanced"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_plan_covers_every_block_once(name, d):
+    check_plan(tables_of(CONFIGS[name], 0), AttnShape(28, 4, d, BS, "f32", "f32"), 256)
+
+
+def test_fp32_segments_take_full_units_in_a_streaming_batch():
+    """fp32 caches have no wide units: a long segment of many beams is cut into narrow-mode units of up to 64 rows,
+    each of which reads its blocks again, also where the batch's private tails are listed in units of fewer rows."""
+    reqs, beams, shared, tail = 4, 63, 450, 3
+    tables = np.zeros((reqs * beams, shared + tail), np.int32)
+    nxt = 0
+    for r in range(reqs):
+        tables[r * beams:(r + 1) * beams, :shared] = nxt + np.arange(shared)
+        nxt += shared
+        for b in range(r * beams, (r + 1) * beams):
+            tables[b, shared:] = nxt + np.arange(tail)
+            nxt += tail
+    lens = np.full(reqs * beams, 16 * (shared + tail), np.int32)
+    desc = tts.make_desc(28, 4, 128, BS, "f32", "f32")
+    rows, _ = tts.tts_plan_units_host(np.arange(reqs + 1, dtype=np.int32) * beams, tables, lens, BS, nxt, desc, 256)
+    of_shared = rows[(rows[:, 2] == 0) & np.isin(rows[:, 4], tables[:, :shared].ravel())]
+    units = {u: 7 * len(set(of_shared[of_shared[:, 0] == u, 3].tolist())) for u in set(of_shared[:, 0].tolist())}
+    assert units and min(units.values()) > 32 and max(units.values()) <= 64
