@@ -73,6 +73,7 @@ constexpr int kGroupRows = 32;  // rows of a narrow unit whose waves work in one
 constexpr int kXcds = 8;  // workgroup k of a launch runs on XCD k % 8
 constexpr int kFewWideRows = 192, kStreamWideRows = 128;  // wide-unit row caps tried besides kMaxWideRows
 constexpr double kCapGain = 0.97;
+constexpr double kSmallWorkUs = 1.5;  // modelled block time per workgroup (half of a unit's fixed part)
 // The merge (a second launch): a fixed cost, and for the beam with the most
 // partial states their writing and reading.
 constexpr double kMergeFixedUs = 3.2;
@@ -488,11 +489,18 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // the merge) is taken. When even the largest units outnumber the
   // workgroups, the targets are taken around the average work.
   std::vector<Tmpl> tm;
-  // Units (of one KV head) that fit the workgroups one each. A batch with
-  // enough beams to fill half of them at four units per beam and head gets
-  // no more than that: few partial states per beam.
-  int32_t fit_units = std::max(1, nbins / hkv);
-  if (4 * S >= fit_units / 2) fit_units = std::min(fit_units, 4 * S);
+  // Units (of one KV head) that fit the workgroups one each. Where there is
+  // little work per workgroup (kSmallWorkUs), a batch with enough beams to
+  // fill half of them at four units per beam and head gets no more than that,
+  // and one with fewer beams no chained units: few partial states per beam.
+  // With more work the bound lengthens the units instead: in trees with long
+  // private tails, 10 beams of 7B shape over fp8 took 49.3 us per call with
+  // it and 30.4 without, 16 of 1.5B shape 21.8 and 18.1. Below the line its
+  // cost is the smaller one (1.5B 16-beam tree 12.4 us per call against
+  // 11.2, 7B shape with 8 beams 12.5 against 11.6; most batches within 1%).
+  const int32_t all_units = std::max(1, nbins / hkv);
+  const int32_t few_units = 4 * S >= all_units / 2 ? std::min(all_units, 4 * S) : all_units;
+  int32_t fit_units = all_units;
   const double target0 = kNarrowFixedUs;  // a unit's fixed part: targets scale what is above it
   auto units_at = [&](double T) {
     make_templates(T, tm);
@@ -536,6 +544,8 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     work = work * hkv / nbins;
     P.work_us = work;
     P.chained = false;
+    const bool small = work < kSmallWorkUs;
+    fit_units = small ? few_units : all_units;
     if (warm && warm->target_us > 0 && warm->work_us > 0) {
       // Warm re-plan: the earlier target, scaled with the work, raised while
       // its units outnumber the workgroups (unless that plan was chained);
@@ -570,7 +580,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     std::vector<Tmpl> cand;
     auto try_target = [&](double T) {
       make_templates(T, cand);
-      if (static_cast<int32_t>(cand.size()) > fit_units && 4 * S < nbins / hkv && est >= 0) return;
+      if (small && static_cast<int32_t>(cand.size()) > fit_units && 4 * S < all_units && est >= 0) return;
       const double e = place(cand, nullptr) + merge_us(cand);
       const bool fit = P.few_states && !over(cand), had_fit = P.few_states && !over(tm);
       if (est >= 0 && (fit != had_fit ? had_fit : e >= est)) return;

@@ -18,7 +18,7 @@ import pytest
 
 import paper_2509_00195_amd as tts
 from paper_2509_00195_amd.tts import PLAN_EXT, PLAN_LIVE, PLAN_SECOND, PLAN_WIDE
-from tts_synth import CONFIGS, AttnShape, build_tree, workload_from_tree
+from tts_synth import CONFIGS, AttnShape, ReqSpec, WorkloadConfig, build_tree, workload_from_tree
 
 BS = 16
 
@@ -191,3 +191,14 @@ def test_fp32_segments_take_full_units_in_a_streaming_batch():
     of_shared = rows[(rows[:, 2] == 0) & np.isin(rows[:, 4], tables[:, :shared].ravel())]
     units = {u: 7 * len(set(of_shared[of_shared[:, 0] == u, 3].tolist())) for u in set(of_shared[:, 0].tolist())}
     assert units and min(units.values()) > 32 and max(units.values()) <= 64
+
+
+@pytest.mark.parametrize("kv,hq,hkv,beams", [("fp8", 12, 2, 16), ("bf16", 12, 2, 16), ("bf16", 32, 8, 4)])
+@pytest.mark.parametrize("cap", [4096, 12000])
+def test_long_tails_of_few_beams_fill_the_workgroups_once(kv, hq, hkv, beams, cap):
+    """Few beams with long private tails: the tails are cut so that the workgroups get about one unit each, however
+    many states that leaves per beam (not half of them, nor three each)."""
+    spec = ReqSpec(beams=beams, branch=4, prompt=(300, 300), step=(64, 256), max_len=cap, rule="balanced")
+    sh = AttnShape(hq, hkv, 128, BS, "bf16", kv)
+    _, units = plan_rows(tables_of(WorkloadConfig("tails", sh, (spec,)), 0), sh, 256)
+    assert 192 <= units <= 256
