@@ -22,10 +22,11 @@
 // scratch stores alone took 8 to 25 us per launch. Against four waves: long
 // chain (fp8) 342 -> 285 us per call, paged 64-beam call 103 -> 92.5, 7B
 // 64-beam tree 23.65 -> 22.5, straggler batch 87.5 -> 85.1, verification of
-// four tokens 46.9 -> 42.5. Bound by the memory where tails stream (balanced
-// tree, 5.3 TB/s of unique KV, unchanged), by LDS reads and vector issue in
-// wide units, and by the units' round trips and the second launch in small
-// batches.
+// four tokens 46.9 -> 42.5; balanced tree unchanged. Where tails stream the
+// middle of a launch runs at the memory's rate (balanced tree: half of its
+// 45 us at about 6 TB/s, 4.7 over the whole launch, the rest its start, its
+// uneven end and the combines); wide units are bound by LDS reads and vector
+// issue, small batches by the units' round trips and the second launch.
 //
 // Products on MFMA, two 16-token blocks ("a pair") at a time, per row tile:
 //   S^T = K Q^T   : 2 x 4 v_mfma_f32_16x16x32_bf16 (M = 16 tokens, N = 16
