@@ -14,7 +14,11 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2509_00195_amd import make_desc, tts_paged_decode_attn, tts_paged_decode_workspace_size
+from oracle.attention import oracle_attn_workload
+from paper_2509_00195_amd import make_desc, tts_paged_decode_attn, tts_paged_decode_workspace_size, tts_prefix_meta_stats
+from paper_2509_00195_amd.runner import PrefixAttention
+from tts_synth import AttnShape, ReqSpec, WorkloadConfig, make_workload
+from tts_synth.device import to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +73,17 @@ def test_merge_slot_counts(kv, d, slots):
             for times in (-1, 1):  # without slot j, and with it twice
                 moved = (total + times * w[j][:, None] * val[j]) / (den + times * w[j][:, None])
                 assert float((moved - ref).abs().max()) > 20 * tol, (b, j)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_merge_of_a_long_beam_through_the_slot_table(d):
+    """A beam alone on the GPU is split over most workgroups: more slots than the table round reads ahead (64). fp32,
+    where leaving out a slot moves the result by more than the tolerance."""
+    spec = ReqSpec(beams=1, branch=1, prompt=(60000, 60000), step=(7, 7), max_len=1 << 20, max_iters=1, snapshot="none")
+    wl = make_workload(WorkloadConfig("long", AttnShape(2, 1, d, 16, "f32", "f32"), (spec,)), 1)
+    pref = PrefixAttention(to_device(wl), wl.req_seq_offsets, wl.block_tables, wl.seq_lens, wl.num_blocks)
+    _, slots = tts_prefix_meta_stats(pref.meta)
+    assert slots > 96  # of the one beam
+    pref.ws.fill_(255)  # every float a NaN
+    ref = oracle_attn_workload(wl)
+    assert float(np.max(np.abs(pref().cpu().numpy() - ref))) <= 2e-6 + 1e-5 * float(np.max(np.abs(ref)))

@@ -258,7 +258,7 @@ def test_private_appends_after_build():
 def test_bad_block_id_gives_nan_row_only(many_rows):
     """A block id outside the pool makes only that beam's row NaN: in the paged path for any table
     entry, in the prefix path for a block appended after the metadata was built (entries in use at
-    build time are validated by tts_build_prefix_meta). Both merge kernels carry the NaN."""
+    build time are validated by tts_build_prefix_meta). The merge carries the NaN, at few rows and at many."""
     wl = _many_rows_workload("bf16", 128) if many_rows else make_workload("1p5b16", 0)
     m = oracle_prefix_meta(wl.req_seq_offsets, wl.block_tables, wl.seq_lens, 16)
     b = 3

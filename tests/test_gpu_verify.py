@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from oracle.attention import oracle_verify_attn
+from oracle.prefix_meta import oracle_prefix_meta
 from paper_2509_00195_amd import (
     TTSError,
     make_desc,
@@ -28,15 +29,15 @@ def _bits(x):
     return torch.from_numpy(np.asarray(x, np.float32)).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
 
 
-def _verify(wl, q_len, seed):
+def _verify(wl, q_len, seed, built=None):
     sh = wl.shape
     rng = np.random.default_rng(seed)
     qf = rng.standard_normal((wl.num_seqs, q_len, sh.num_q_heads, sh.head_dim)).astype(np.float32)
     q = qf if sh.q_dtype == "f32" else _bits(qf)
     x = to_device(wl)
     desc = make_desc(sh.num_q_heads, sh.num_kv_heads, sh.head_dim, q_dtype=sh.q_dtype, kv_dtype=sh.kv_dtype)
-    meta = tts_build_verify_meta(wl.req_seq_offsets, wl.block_tables, wl.seq_lens, q_len, 16, wl.num_blocks,
-                                 desc=desc)
+    meta = tts_build_verify_meta(wl.req_seq_offsets, wl.block_tables, wl.seq_lens if built is None else built, q_len,
+                                 16, wl.num_blocks, desc=desc)
     wsb = tts_prefix_decode_workspace_size(desc, meta)
     ws = torch.zeros(max(wsb, 1), dtype=torch.uint8, device="cuda")
     out = torch.zeros((wl.num_seqs, q_len, sh.num_q_heads, sh.head_dim), dtype=torch.float32, device="cuda")
@@ -57,6 +58,19 @@ def test_verify_parity(name, q_len):
     e = float(np.max(np.abs(got - ref)))
     print(f"verify {name} q_len {q_len}: err {e:.2e}", flush=True)
     assert np.isfinite(got).all() and e <= TOL[wl.shape.kv_dtype]
+
+
+@pytest.mark.parametrize("q_len", [2, 5])
+def test_verify_after_growth(q_len):
+    """Beams that gained up to 40 tokens since the verification metadata was built: every query's own length."""
+    wl = make_workload("1p5b16", 4)
+    m = oracle_prefix_meta(wl.req_seq_offsets, wl.block_tables, wl.seq_lens, 16)
+    grown = np.arange(wl.num_seqs) * 40 // (wl.num_seqs - 1)
+    built = np.maximum(m["tail_lblock"] * 16 + q_len, wl.seq_lens - grown).astype(np.int32)
+    built = np.minimum(built, wl.seq_lens)
+    assert (built < wl.seq_lens - 16).any()
+    got, ref, _, _, _ = _verify(wl, q_len, 7, built)
+    assert np.isfinite(got).all() and float(np.max(np.abs(got - ref))) <= TOL["bf16"]
 
 
 def test_verify_parity_fp8():
