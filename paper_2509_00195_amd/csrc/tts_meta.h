@@ -78,7 +78,8 @@ struct WorkPlan {
   bool chained = false;
   int32_t wide_rows = 0;    // the row caps of the wide and the narrow units
   int32_t narrow_rows = 0;  // the plan chose
-  bool few_states = false;  // units chosen so that the states fit the scratch array
+  bool few_units = false;   // segments that fit a narrow unit stay in the narrow list
+  bool few_states = false;  // such units chosen so that the states fit the scratch array
   double few_ratio = 0;     // states of such a plan over those of the fastest one (0: never made)
 };
 

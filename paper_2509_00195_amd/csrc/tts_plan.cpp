@@ -73,6 +73,11 @@ constexpr int kGroupRows = 32;  // rows of a narrow unit whose waves work in one
 constexpr int kXcds = 8;  // workgroup k of a launch runs on XCD k % 8
 constexpr int kFewWideRows = 192, kStreamWideRows = 128;  // wide-unit row caps tried besides kMaxWideRows
 constexpr double kCapGain = 0.97;
+// Units of a chain beyond this many per workgroup are weighed against fewer,
+// larger ones, with this much more for each of them than the terms above say
+// (fitted to 40 batches of 600 to 3,072 beams in both plans: 2.5 us, the
+// fewest wrong choices at 3).
+constexpr double kLongChain = 4, kChainUnitUs = 3.0;
 constexpr double kSmallWorkUs = 1.5;  // modelled block time per workgroup (half of a unit's fixed part)
 // The merge (a second launch): a fixed cost, and for the beam with the most
 // partial states their writing and reading.
@@ -251,10 +256,10 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   auto list_items = [&]() {
     // A segment of more rows than one wave group takes is cut into units of
     // its own (left to narrow units of two groups, its blocks are read twice:
-    // 7B 64-beam tree 24.4 us per call against 23.1; fp32 caches: of more
-    // than a narrow unit takes; also where states are to be few: beams'
-    // blocks beside their segment's take no state of their own).
-    const int32_t most = wide_mode && !P.few_states ? narrow_beams(kGroupRows) : RB;
+    // 7B 64-beam tree 24.4 us per call against 23.1; fp32 caches, and plans
+    // of few units: of more than a narrow unit takes, beams' blocks beside
+    // their segment's need no unit and no state of their own).
+    const int32_t most = wide_mode && !P.few_units ? narrow_beams(kGroupRows) : RB;
     for (int32_t s = 0; s < nseg; ++s) wide[s] = (m.seg_beam_end[s] - m.seg_beam_begin[s]) > most;
     items.clear();
     for (auto& t : top) {
@@ -616,8 +621,8 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // does is replaced by one of larger units where that fits (512 to 3072
   // beams: up to 1.3 times the bytes without this rule). Callers with a
   // workspace of their own lose nothing by it: of five batches of 1,920 to
-  // 3,072 beams, 202, 240, 256, 176 and 233 us per call with the larger units
-  // and 227, 264, 275, 229 and 233 with those they replace.
+  // 3,072 beams, 202, 246, 258, 173 and 234 us per call with the larger units
+  // and 227, 268, 277, 228 and 242 with those they replace.
   auto set_caps = [&](int32_t wide_rows, int32_t narrow_rows) {
     P.wide_rows = wide_rows;
     P.narrow_rows = narrow_rows;
@@ -625,11 +630,15 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     RW = wide_beams(wide_rows);
     list_items();
   };
+  // The same larger units are weighed wherever many units are chained to a
+  // workgroup (237 requests of 8 beams, 7B shape: 107 us per call against
+  // 121; 44 of 48 beams, 14 heads of 2: 69 against 77).
   // A warm re-plan keeps the choice too, unless the other one would now fit
   // (judged by few_ratio): a batch that shrank gets its fastest plan back,
   // and one whose plan outgrows the array is planned anew where larger units
   // may fit.
   if (warm && warm->target_us > 0 && warm->work_us > 0 && warm->wide_rows > 0) {
+    P.few_units = warm->few_units;
     P.few_states = warm->few_states;
     P.few_ratio = warm->few_ratio;
     set_caps(warm->wide_rows, warm->narrow_rows);
@@ -642,17 +651,19 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     warm = nullptr;
   }
   if (!warm) {
-    P.few_states = false;
+    P.few_units = P.few_states = false;
     P.few_ratio = 0;
     set_caps(streaming ? kStreamWideRows : kFewWideRows, streaming && wide_mode ? kGroupRows : kMaxRows);
     double best = search();
     // Runs the search at other caps and keeps its plan if keep (of its
     // modelled time) says so, else restores the plan at hand.
-    auto try_caps = [&](int32_t wide_rows, int32_t narrow_rows, auto keep) {
+    auto try_caps = [&](int32_t wide_rows, int32_t narrow_rows, bool few_units, auto keep) {
       std::vector<Tmpl> tm0 = tm;
+      const bool few0 = P.few_units;
       const int32_t wide0 = P.wide_rows, narrow0 = P.narrow_rows;
       const double target0 = P.target_us, work0 = P.work_us;
       const bool chained0 = P.chained;
+      P.few_units = few_units;
       set_caps(wide_rows, narrow_rows);
       const double alt = search();
       if (keep(alt)) {
@@ -660,6 +671,7 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
         return;
       }
       P.few_states = false;
+      P.few_units = few0;
       set_caps(wide0, narrow0);
       tm.swap(tm0);
       P.target_us = target0;
@@ -674,13 +686,20 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       const int32_t G = m.seg_beam_end[s] - m.seg_beam_begin[s];
       if (wide[s] && (G + RW - 1) / RW != (G + most - 1) / most) chunks_differ = true;
     }
-    if (chunks_differ) try_caps(kMaxWideRows, P.narrow_rows, [&](double us) { return us < kCapGain * best; });
+    if (chunks_differ) try_caps(kMaxWideRows, P.narrow_rows, false, [&](double us) { return us < kCapGain * best; });
     for (int32_t rows : {kGroupRows, kGroupRows / 2})
-      if (cm.f32) try_caps(P.wide_rows, rows, [&](double us) { return us < kCapGain * best; });
+      if (cm.f32) try_caps(P.wide_rows, rows, false, [&](double us) { return us < kCapGain * best; });
+    // Long chains of units: fewer, larger ones where they model faster with
+    // what the model leaves out per unit of a chain.
+    const double chain = static_cast<double>(tm.size()) * hkv / nbins;
+    if (wide_mode && streaming && chain > kLongChain)
+      try_caps(kMaxWideRows, kMaxRows, true, [&](double us) {
+        return us + kChainUnitUs * tm.size() * hkv / nbins < best + kChainUnitUs * chain;
+      });
     if (over(tm)) {
       const double rows = rows_of(tm);
       P.few_states = true;
-      try_caps(kMaxWideRows, kMaxRows, [&](double) {
+      try_caps(kMaxWideRows, kMaxRows, true, [&](double) {
         P.few_ratio = rows_of(tm) / rows;
         return !over(tm);
       });

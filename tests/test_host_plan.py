@@ -202,3 +202,20 @@ def test_long_tails_of_few_beams_fill_the_workgroups_once(kv, hq, hkv, beams, ca
     sh = AttnShape(hq, hkv, 128, BS, "bf16", kv)
     _, units = plan_rows(tables_of(WorkloadConfig("tails", sh, (spec,)), 0), sh, 256)
     assert 192 <= units <= 256
+
+
+def test_many_small_requests_are_units_of_their_own():
+    """Hundreds of requests of eight beams with short prompts and tails: chained by the dozen, units have to be few. A
+    request (56 rows of one KV head) is about one unit, not one for its prompt and one for every four beams' tails."""
+    reqs, beams, prompt, tail = 240, 8, 5, 4
+    tables = np.zeros((reqs * beams, prompt + tail), np.int32)
+    nxt = 0
+    for r in range(reqs):
+        for b in range(r * beams, (r + 1) * beams):
+            tables[b, :prompt] = nxt + np.arange(prompt)
+            tables[b, prompt:] = nxt + prompt + (b - r * beams) * tail + np.arange(tail)
+        nxt += prompt + beams * tail
+    lens = np.full(reqs * beams, 16 * (prompt + tail) - 3, np.int32)
+    desc = tts.make_desc(28, 4, 128, BS, "bf16", "bf16")
+    _, units = tts.tts_plan_units_host(np.arange(reqs + 1, dtype=np.int32) * beams, tables, lens, BS, nxt, desc, 256)
+    assert units <= 1.5 * reqs * 4

@@ -18,27 +18,27 @@ DRIVER = r"""
 #include <cstring>
 #include "tts_meta.h"
 using namespace tts;
-// n requests of 64 beams: a prompt of 12 blocks, groups of 8 beams (5 blocks), pairs (4), 3 private blocks.
+// n requests of 64 beams: a prompt of 12 blocks, groups of 8 beams (40 blocks), pairs (4), 3 private blocks.
 static HostMeta batch(int n) {
-  std::vector<int32_t> tab(n * 64 * 24, -1), len, off{0};
-  int32_t nxt = 0, prompt[12], mid[5], pair[4];
+  std::vector<int32_t> tab(n * 64 * 59, -1), len, off{0};
+  int32_t nxt = 0, prompt[12], mid[40], pair[4];
   for (int r = 0; r < n; ++r) {
     for (auto& x : prompt) x = nxt++;
     for (int b = 0; b < 64; ++b) {
       if (b % 8 == 0) for (auto& x : mid) x = nxt++;
       if (b % 2 == 0) for (auto& x : pair) x = nxt++;
-      int32_t* row = tab.data() + (r * 64 + b) * 24;
+      int32_t* row = tab.data() + (r * 64 + b) * 59;
       std::memcpy(row, prompt, sizeof prompt);
       std::memcpy(row + 12, mid, sizeof mid);
-      std::memcpy(row + 17, pair, sizeof pair);
-      for (int k = 21; k < 24; ++k) row[k] = nxt++;
-      len.push_back(16 * 24 - 5);
+      std::memcpy(row + 52, pair, sizeof pair);
+      for (int k = 56; k < 59; ++k) row[k] = nxt++;
+      len.push_back(16 * 59 - 5);
     }
     off.push_back((r + 1) * 64);
   }
   MetaInput in;
   in.num_reqs = n, in.req_seq_offsets = off.data(), in.num_seqs = 64 * n, in.block_tables = tab.data();
-  in.max_blocks = 24, in.seq_lens = len.data(), in.num_blocks = nxt;
+  in.max_blocks = 59, in.seq_lens = len.data(), in.num_blocks = nxt;
   HostMeta m;
   std::string err;
   if (build_host_meta(in, &m, &err)) std::abort();
