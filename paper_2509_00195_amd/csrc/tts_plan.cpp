@@ -87,17 +87,11 @@ constexpr double kMergeSlotUs = 0.06;
 int tiles_of(int rows) { return (rows + 15) / 16; }
 
 // The blocks of a narrow unit: how many, how many with rows of both wave
-// groups, which both read, and how many of each row tile.
+// groups, which both read; for fp32 caches also how many reads the busiest row
+// tile and the first two tiles need.
 struct NarrowLoad {
   int blocks = 0, span = 0;
-  int tile[kMaxRows / 16] = {};
-  // n blocks of the unit's rows [r0, r1).
-  NarrowLoad& add(int n, int r0, int r1) {
-    blocks += n;
-    if (r0 < kGroupRows && r1 > kGroupRows) span += n;
-    for (int t = r0 / 16; 16 * t < r1; ++t) tile[t] += n;
-    return *this;
-  }
+  int most = 0, low = 0;
 };
 
 struct CostModel {
@@ -108,8 +102,7 @@ struct CostModel {
   // Narrow units: the waves split the block pairs, every wave runs every tile.
   double narrow_us(const NarrowLoad& x, int rows) const {
     if (f32) {
-      const int most = std::max(std::max(x.tile[0], x.tile[1]), std::max(x.tile[2], x.tile[3]));
-      const int tiles = rows > 32 ? 4 * most : x.tile[0] + x.tile[1];
+      const int tiles = rows > 32 ? 4 * x.most : x.low;
       return kNarrowFixedUs + (rows > 16 ? kGroupsUs : 0.0) +
              std::max(x.blocks * narrow_block_us(), tiles * f32_tile_us()) + rows * row_us();
     }
@@ -155,6 +148,7 @@ struct NItem {
   int32_t p0, p1;
   int32_t valid;
   uint32_t flags;
+  int32_t run = 1;  // from here, plain blocks of the same beams (they follow each other)
 };
 
 struct Work {
@@ -282,6 +276,11 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
         push_sorted(tmp);
       }
     }
+    for (size_t k = items.size(); k-- > 1;) {
+      NItem& x = items[k - 1];
+      const NItem& y = items[k];
+      if (x.flags == 0 && y.flags == 0 && x.p0 == y.p0 && x.p1 == y.p1) x.run = y.run + 1;
+    }
   };
 
   // ---- units for a target unit time T ------------------------------------
@@ -291,7 +290,9 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
   // least share of the modelled time, its units' time over the workgroups
   // plus the merge of its pieces' states (else the fastest). The narrow list
   // is cut greedily into units that fit T.
-  auto narrow_us = [&](int32_t blocks, int32_t rows) { return cm.narrow_us(NarrowLoad().add(blocks, 0, rows), rows); };
+  auto narrow_us = [&](int32_t blocks, int32_t rows) {  // every block for all rows
+    return cm.narrow_us({blocks, rows > kGroupRows ? blocks : 0, blocks, std::min(2, tiles_of(rows)) * blocks}, rows);
+  };
   auto make_templates = [&](double T, std::vector<Tmpl>& tm) {
     tm.clear();
     int32_t ngroups = 0;
@@ -349,9 +350,19 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
     Tmpl cur;
     // The open unit's static items, and its LIVE and extension items.
     NarrowLoad load;
+    int32_t tile[kMaxRows / 16] = {};  // fp32: blocks of each row tile
     int32_t nlive_ext = 0;
-    auto with = [&](NarrowLoad x, const NItem& it, int32_t lo) {
-      return (it.flags & kEntExt) ? x : x.add(1, (it.p0 - lo) * g, (it.p1 - lo) * g);
+    auto with = [&](const NItem& it, int32_t lo, int32_t n) {  // n blocks of the item's beams more
+      NarrowLoad x = load;
+      if (it.flags & kEntExt) return x;
+      const int32_t r0 = (it.p0 - lo) * g, r1 = (it.p1 - lo) * g;
+      x.blocks += n;
+      if (r0 < kGroupRows && r1 > kGroupRows) x.span += n;
+      for (int32_t t = r0 / 16; cm.f32 && 16 * t < r1; ++t) {
+        x.most = std::max(x.most, tile[t] + n);
+        x.low += t < 2 ? n : 0;
+      }
+      return x;
     };
     auto flush = [&]() {
       if (cur.b == cur.a) return;
@@ -359,25 +370,32 @@ void build_work_plan(const HostMeta& m, const PlanShape& shape, WorkPlan* plan, 
       tm.push_back(cur);
       cur.a = cur.b;
       load = NarrowLoad();
+      std::fill(tile, tile + kMaxRows / 16, 0);
       nlive_ext = 0;
     };
-    for (int32_t k = 0; k < static_cast<int32_t>(items.size()); ++k) {
+    // (Costs grow with the blocks: a run whose last block fits, fits.)
+    for (int32_t k = 0, n = 0; k < static_cast<int32_t>(items.size()); k += n) {
       const NItem& it = items[k];
       const int32_t live = (it.flags & (kEntLive | kEntExt)) ? 1 : 0;
-      if (cur.b > cur.a) {
-        const int32_t lo = std::min(cur.lo, it.p0), hi = std::max(cur.hi, it.p1);
-        const bool fits = hi - lo <= RB && cur.b - cur.a + 1 <= kMaxUnitEntries && nlive_ext + live <= kMaxEntries &&
-                          cm.narrow_us(with(load, it, lo), (hi - lo) * g) <= T;
-        if (!fits) flush();
+      const bool open = cur.b > cur.a;
+      const int32_t lo = open ? std::min(cur.lo, it.p0) : it.p0, hi = open ? std::max(cur.hi, it.p1) : it.p1;
+      auto fits = [&](int32_t m) {
+        return hi - lo <= RB && cur.b - cur.a + m <= kMaxUnitEntries && nlive_ext + live <= kMaxEntries &&
+               cm.narrow_us(with(it, lo, m), (hi - lo) * g) <= T;
+      };
+      n = it.run;
+      if (n > 1 && !fits(n)) n = 1;
+      if (n == 1 && open && !fits(1)) {
+        flush();
+        n = 0;  // the item opens the next unit
+        continue;
       }
-      if (cur.b == cur.a) {
-        cur.lo = it.p0;
-        cur.hi = it.p1;
-      }
-      cur.lo = std::min(cur.lo, it.p0);
-      cur.hi = std::max(cur.hi, it.p1);
-      cur.b = k + 1;
-      load = with(load, it, cur.lo);
+      cur.lo = lo;
+      cur.hi = hi;
+      cur.b = k + n;
+      load = with(it, lo, n);
+      for (int32_t t = (it.p0 - lo) * g / 16; cm.f32 && !(it.flags & kEntExt) && 16 * t < (it.p1 - lo) * g; ++t)
+        tile[t] += n;
       nlive_ext += live;
     }
     flush();
