@@ -12,7 +12,7 @@ import pytest
 
 from paper_2509_00195_amd.build import CSRC
 
-DRIVER = r"""
+PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -65,12 +65,12 @@ LIMIT = 64 << 20
 @pytest.fixture(scope="module")
 def replan(tmp_path_factory):
     d = tmp_path_factory.mktemp("replan")
-    (d / "driver.cpp").write_text(DRIVER)
-    subprocess.run(["g++", "-O2", "-std=c++17", f"-I{CSRC}", str(d / "driver.cpp"), f"{CSRC}/tts_meta.cpp",
-                    f"{CSRC}/tts_plan.cpp", "-o", str(d / "driver")], check=True)
+    (d / "replan.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=c++17", f"-I{CSRC}", str(d / "replan.cpp"), f"{CSRC}/tts_meta.cpp",
+                    f"{CSRC}/tts_plan.cpp", "-o", str(d / "replan")], check=True)
 
     def run(*requests):
-        r = subprocess.run([str(d / "driver"), *map(str, requests)], check=True, capture_output=True, text=True)
+        r = subprocess.run([str(d / "replan"), *map(str, requests)], check=True, capture_output=True, text=True)
         return [tuple(int(x) for x in line.split()) for line in r.stdout.splitlines()]
 
     return run
